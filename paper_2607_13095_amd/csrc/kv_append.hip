@@ -5,127 +5,285 @@
 // and the ring overwrite is the out-of-window eviction that follows every chunk
 // and every decode step ("SWA-Aware Prefix Cache Tree").
 //
-// One workgroup handles 8 consecutive tokens of the flattened batch for one KV
-// head. A token's K row goes to the pool as sixteen 16-byte pieces (the K
-// blocks are stored in MFMA-operand slabs); V pages are stored as transposed
-// blocks of B = min(PG, 32) keys ([D][B] per block and head), so 8 tokens that
-// land on 8 consecutive, 8-aligned slots of one page are written as one 16-byte
-// store per dim; anything else falls back to 2-byte stores.
+// Bound by moving the rows: every row is read once and written once. What
+// decides the rate is the width of the V stores, since a V block is transposed
+// ([D][B] keys) and a token's column in it is 128 scattered 2-byte elements.
+// The work is therefore cut along the pool's blocks, not along the batch: for
+// each aligned run of 32 positions of one sequence and KV head, one workgroup
+// reads its rows (64-byte runs of 16 rows per load instruction), transposes V
+// in registers with lane swaps, and writes whole 16-byte pieces, the K block as
+// contiguous 1 KiB runs and V as full 64-byte rows, whatever the sequences'
+// alignment in the batch. Only the first and last 8 keys of a sequence's append
+// can be partial pieces (2-byte stores). Cutting at 8 tokens of the batch
+// instead left 2-byte stores for every sequence whose position and batch
+// offset differ modulo 8.
+// 12.3K tokens in 8 sequences at unaligned positions, 8 heads, PG 64 (101 MB
+// read and written): 92 -> 25 us, 4.0 TB/s (a large device copy: 4.7).
+// Sequences of fewer than 16 new tokens (a decode step's single token) are
+// scattered token by token, all tokens of a tile at once.
 #include "hswa_common.h"
 #include "hswa_launch.h"
 
 namespace hswa {
 namespace {
 
-constexpr int kTokPerBlock = 8;
 constexpr int kThreads = 256;
 constexpr int kLdsSeqs = 4096;  // batches up to this size search cu_seqlens in LDS
+constexpr int kRun = 32;        // positions of an aligned run
 
-// Sequence of flattened token t: the b with cu[b] <= t < cu[b+1] (-1 if none).
-// `cu` is the LDS copy of cu_seqlens when it fits, else the global array.
-__device__ int find_seq(const int32_t *cu, int ns, int t) {
+// Sequence of flattened token t: the b with cu(b) <= t < cu(b + 1) (-1 if none).
+template <typename Cu>
+__device__ __forceinline__ int find_seq(Cu cu, int ns, int t) {
   int lo = 0, hi = ns;  // answer in [0, ns)
-  if (ns <= 0 || t < cu[0] || t >= cu[ns]) return -1;
   while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (cu[mid] <= t) lo = mid; else hi = mid;
+    const int mid = (lo + hi) >> 1;
+    if (cu(mid) <= t) lo = mid; else hi = mid;
   }
-  return lo;
+  return t >= cu(lo) && t < cu(lo + 1) ? lo : -1;
 }
 
-__device__ int64_t slot_of_token(const AppendParams &p, const int32_t *cu, int t) {
-  int b;
-  int64_t j, len_after;
-  if (p.ctx_lens) {  // decode step: token t is sequence t's
-    b = t;
-    len_after = min(p.ctx_lens[b], p.max_ctx);
-    j = len_after - 1;
-  } else {
-    b = find_seq(cu, p.ns, t);
-    if (b < 0) return -1;
-    const int64_t start = p.start_pos[b];
-    j = start + (t - cu[b]);
-    len_after = start + (cu[b + 1] - cu[b]);
-  }
-  if (j < 0) return -1;
-  const PoolView &pv = p.pool;
-  const int64_t pg = int64_t(1) << pv.pg_shift;
-  int64_t lp = j >> pv.pg_shift;
-  if (pv.ring > 0) {
-    if (j < len_after - pv.ring * pg) return -1;  // the ring keeps the latest R*PG
-    lp = lp % pv.ring;
-  }
+// Physical page of logical page lp >= 0 of sequence b, -1 if the table has none.
+__device__ __forceinline__ int64_t page_of(const PoolView &pv, int b, int64_t lp) {
+  if (pv.ring > 0) lp = (uint32_t)lp % (uint32_t)pv.ring;  // lp < 2^33 / 16
   if (lp >= pv.stride) return -1;
   const int64_t page = pv.table[int64_t(b) * pv.stride + lp];
-  if (page < 0 || page >= pv.num_pages) return -1;
-  return page * pg + (j & (pg - 1));
+  return page >= 0 && page < pv.num_pages ? page : -1;
 }
 
-// Grid: (groups of 8 tokens, KV heads). Each workgroup moves 8 tokens of one
-// KV head: 8 K rows of 256 bytes and 8 x 128 V values.
+// The same for a wave-uniform b and lp, read through the scalar cache (the
+// kernel writes no table).
+__device__ __forceinline__ int uniform_page(const PoolView &pv, int b, int lp) {
+  if (pv.ring > 0) lp %= pv.ring;
+  if (lp >= pv.stride) return -1;
+  typedef __attribute__((address_space(4))) const int32_t const_i32;
+  const int page = ((const_i32 *)pv.table)[(int64_t)b * pv.stride + lp];
+  return page >= 0 && page < pv.num_pages ? page : -1;
+}
+
+// 4 x 4 transpose of dwords across the lanes l, l ^ 16, l ^ 32, l ^ 48: the
+// lane in 16-lane row m enters with dword j of its row m in t[j] and leaves
+// with dword m of rows 0..3 in w[0..3].
+__device__ __forceinline__ void transpose4(const u32x4 &t, uint32_t *w) {
+  const auto a = __builtin_amdgcn_permlane32_swap(t[0], t[2], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(t[1], t[3], false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap((uint32_t)a[0], (uint32_t)b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap((uint32_t)a[1], (uint32_t)b[1], false, false);
+  w[0] = (uint32_t)c[0];
+  w[1] = (uint32_t)c[1];
+  w[2] = (uint32_t)d[0];
+  w[3] = (uint32_t)d[1];
+}
+
+// One workgroup per (tile of kTok consecutive tokens of the flattened batch, KV
+// head). It scatters the tile's tokens of short sequences, and writes every
+// aligned run of a long sequence whose first appended token lies in the tile
+// (the run's other tokens may lie past it; no other workgroup writes them).
+// 8-token tiles scatter every sequence.
+template <int kTok>
 __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
-  __shared__ int64_t s_slot[kTokPerBlock];
+  // sequences of at least this many new tokens are written by runs
+  constexpr int kLong = kTok == kRun ? kRun / 2 : INT32_MAX;
   __shared__ int32_t s_cu[kLdsSeqs + 1];
-  const int t0 = blockIdx.x * kTokPerBlock;
-  const int g = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int ntok = min(kTokPerBlock, p.total_tokens - t0);
-  // One coalesced load of cu_seqlens instead of a chain of dependent loads in
-  // the binary search.
-  const bool lds_cu = p.ns <= kLdsSeqs && !p.ctx_lens;
-  if (lds_cu) {
-    for (int i = tid; i <= p.ns; i += kThreads) s_cu[i] = p.cu_seqlens[i];
-  }
-  __syncthreads();
-  if (tid < ntok) {
-    const int64_t s = slot_of_token(p, lds_cu ? s_cu : p.cu_seqlens, t0 + tid);
-    s_slot[tid] = s;
-    if (p.slot_out && g == 0) p.slot_out[t0 + tid] = s;
-  }
-  __syncthreads();
-
   const PoolView &pv = p.pool;
-  const int pg = 1 << pv.pg_shift;
   const int hkv = p.hkv;
-  constexpr int kRow16 = kHeadDim / 8;  // 16-byte pieces per K row
+  const int tile = (int)(blockIdx.x / (unsigned)hkv);
+  const int g = (int)(blockIdx.x - (unsigned)tile * (unsigned)hkv);  // heads of a token next to each other: whole rows
+  const int t0 = tile * kTok;
+  const int tid = threadIdx.x;
+  const int lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int pg = 1 << pv.pg_shift;
 
-  // K rows: threads 0..127 copy the 16-byte pieces of 8 rows.
-  if (tid < kTokPerBlock * kRow16) {
-    const int tok = tid / kRow16, c = tid % kRow16;
-    const int64_t s = tok < ntok ? s_slot[tok] : -1;
-    if (s >= 0) {
-      const int64_t page = s >> pv.pg_shift, off = s & (pg - 1);
-      const u32x4 v = ldg128(p.k_new + ((int64_t)(t0 + tok) * hkv + g) * kHeadDim + c * 8);
-      stg128(pv.k_pool + k_offset(pv, page, hkv, g, (int)off, c * 8), v);
+  // The pieces of a short sequence's rows this thread stores. An 8-token tile
+  // (mostly single tokens) loads them at once, next to the lengths and the
+  // table, so that only the stores wait for the slots.
+  constexpr bool kEarly = kTok == 8;
+  constexpr int kSK = (kTok * 16 + kThreads - 1) / kThreads, kSV = kTok * kHeadDim / kThreads;
+  u32x4 ek[kSK];
+  uint16_t ev[kSV];
+  if constexpr (kEarly) {
+#pragma unroll
+    for (int i = 0; i < kSK; ++i) {
+      const int tk = min(t0 + (((tid + kThreads * i) >> 4) & (kTok - 1)), p.total_tokens - 1);
+      ek[i] = ldg128(p.k_new + ((int64_t)tk * hkv + g) * kHeadDim + (tid & 15) * 8);
+    }
+#pragma unroll
+    for (int i = 0; i < kSV; ++i) {
+      const int tk = min(t0 + ((tid + kThreads * i) >> kHeadDimShift), p.total_tokens - 1);
+      ev[i] = p.v_new[((int64_t)tk * hkv + g) * kHeadDim + (tid & (kHeadDim - 1))];
     }
   }
 
-  // V: transposed pages.
-  bool run = ntok == kTokPerBlock && s_slot[0] >= 0 && (s_slot[0] & 7) == 0;
-#pragma unroll
-  for (int i = 1; i < kTokPerBlock; ++i) run = run && s_slot[i] == s_slot[0] + i;
-  if (run) {
-    // 8 consecutive, 8-aligned slots of one page: one 16-byte store per dim
-    if (tid < kHeadDim) {
-      const int d = tid;
-      const int64_t page = s_slot[0] >> pv.pg_shift, off = s_slot[0] & (pg - 1);
-      const uint16_t *src = p.v_new + ((int64_t)t0 * hkv + g) * kHeadDim + d;
-      u32x4 w;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t lo = src[(int64_t)(2 * k) * hkv * kHeadDim];
-        const uint32_t hi = src[(int64_t)(2 * k + 1) * hkv * kHeadDim];
-        w[k] = lo | (hi << 16);
-      }
-      stg128(pv.v_pool + v_offset(pv, page, hkv, g, (int)off, d), w);
+  // Lane i < kTok of every wave holds token t0 + i: its sequence b, the
+  // sequence's first token tb, its end te and the position of its first token.
+  // The lengths are read once, coalesced, instead of by a chain of dependent
+  // loads in the binary search: up to 63 sequences in the lanes (with their
+  // start positions), larger batches in LDS.
+  const int t = t0 + lane;
+  const bool tok_ok = lane < kTok && t < p.total_tokens;
+  int b = -1, tb = 0, te = 0;
+  int64_t start = 0;
+  if (p.ctx_lens) {  // decode step: token t is sequence t's
+    if (tok_ok) {
+      b = t;
+      tb = t;
+      te = t + 1;
+      start = (int64_t)min(p.ctx_lens[b], p.max_ctx) - 1;
     }
+  } else if (p.ns < kWave) {
+    const int cul = p.cu_seqlens[min(lane, p.ns)];
+    const int spl = p.start_pos[min(lane, p.ns - 1)];
+    int lo = 0;  // the last b with cu[b] <= t, by halving (all lanes take part in the shuffles)
+#pragma unroll
+    for (int step = kWave / 2; step > 0; step >>= 1) {
+      const int mid = lo + step;
+      const int c = __shfl(cul, min(mid, p.ns), kWave);
+      if (mid < p.ns && c <= t) lo = mid;
+    }
+    tb = __shfl(cul, lo, kWave);
+    te = __shfl(cul, lo + 1, kWave);
+    start = __shfl(spl, lo, kWave);
+    if (tok_ok && t >= tb && t < te) b = lo;
   } else {
-    for (int i = tid; i < ntok * kHeadDim; i += kThreads) {
-      const int tok = i / kHeadDim, d = i - tok * kHeadDim;
-      const int64_t s = s_slot[tok];
-      if (s < 0) continue;
-      const int64_t page = s >> pv.pg_shift, off = s & (pg - 1);
-      pv.v_pool[v_offset(pv, page, hkv, g, (int)off, d)] = p.v_new[((int64_t)(t0 + tok) * hkv + g) * kHeadDim + d];
+    const bool lds_cu = p.ns <= kLdsSeqs;
+    if (lds_cu) {
+      for (int i = tid; i <= p.ns; i += kThreads) s_cu[i] = p.cu_seqlens[i];
+      __syncthreads();
+    }
+    if (tok_ok) {
+      b = lds_cu ? find_seq([&](int i) { return s_cu[i]; }, p.ns, t)
+                 : find_seq([&](int i) { return p.cu_seqlens[i]; }, p.ns, t);
+      if (b >= 0) {
+        tb = lds_cu ? s_cu[b] : p.cu_seqlens[b];
+        te = lds_cu ? s_cu[b + 1] : p.cu_seqlens[b + 1];
+        start = p.start_pos[b];
+      }
+    }
+  }
+  const int64_t j = start + (t - tb);
+  const bool is_long = b >= 0 && te - tb >= kLong;
+
+  // Slots: every token's for the mapping, and those of the short sequences.
+  const bool scatter = b >= 0 && !is_long;
+  const uint64_t smask = __builtin_amdgcn_ballot_w64(scatter);
+  const bool slots = p.slot_out && g == 0 && wave == 0;
+  int64_t slot = -1;
+  if (slots || smask != 0) {
+    if (b >= 0 && j >= 0 && !(pv.ring > 0 && j < start + (te - tb) - (int64_t)pv.ring * pg)) {
+      const int64_t page = page_of(pv, b, j >> pv.pg_shift);
+      if (page >= 0) slot = page * pg + (j & (pg - 1));
+    }
+    if (slots && tok_ok) p.slot_out[t] = slot;
+  }
+
+  // Short sequences: K rows as sixteen 16-byte pieces, V element by element.
+  if (smask != 0) {
+    const int64_t sslot = scatter ? slot : -1;
+#pragma unroll
+    for (int i = 0; i < kSK; ++i) {
+      const int idx = tid + kThreads * i;
+      const int tok = (idx >> 4) & (kTok - 1), c = idx & 15;
+      const int64_t s = __shfl(sslot, tok, kWave);
+      if (idx < kTok * 16 && s >= 0) {
+        const u32x4 v = kEarly ? ek[i] : ldg128(p.k_new + ((int64_t)(t0 + tok) * hkv + g) * kHeadDim + c * 8);
+        stg128(pv.k_pool + k_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), c * 8), v);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kSV; ++i) {
+      const int idx = tid + kThreads * i;
+      const int tok = idx >> kHeadDimShift, d = idx & (kHeadDim - 1);
+      const int64_t s = __shfl(sslot, tok, kWave);
+      if (s >= 0) {
+        const uint16_t v = kEarly ? ev[i] : p.v_new[((int64_t)(t0 + tok) * hkv + g) * kHeadDim + d];
+        pv.v_pool[v_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), d)] = v;
+      }
+    }
+  }
+
+  if constexpr (kTok != kRun) return;
+  // Long sequences: the runs that start in this tile (a sequence's first token,
+  // or a position that is a multiple of kRun).
+  const bool two = pv.pg_shift == 4;
+  uint64_t runs = __builtin_amdgcn_ballot_w64(is_long && (t == tb || (j & (kRun - 1)) == 0));
+  while (runs != 0) {
+    const int l = __builtin_ctzll(runs);
+    runs &= runs - 1;
+    const int rb = __builtin_amdgcn_readlane(b, l);
+    const int rte = __builtin_amdgcn_readlane(te, l);
+    const int64_t rj = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(j >> 32), l) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((int)j, l));
+    const int64_t base = rj & ~(int64_t)(kRun - 1);
+    const int first = (int)(rj - base);              // key of token t0 + l in the run
+    const int nkeys = min(kRun, first + min(rte, p.total_tokens) - (t0 + l));  // key of the first token past the new ones
+    // the ring keeps the latest R*PG positions; positions before 0 do not exist
+    int64_t keep_lo = 0;
+    if (pv.ring > 0) keep_lo = max(keep_lo, rj + (rte - (t0 + l)) - (int64_t)pv.ring * pg);
+    const int klo = (int)min((int64_t)kRun, max((int64_t)first, keep_lo - base));
+    if (klo >= nkeys) continue;  // nothing of the run is kept
+    const int tk0 = t0 + l - first;  // token of key 0 (read from key klo on only)
+
+    // loads: K pieces in pool order (16 keys x 64 bytes a load), V pieces of
+    // keys 8 kg + 4 i + m, dims 32 wave + 8 c .. +7 (kg = lane % 4,
+    // c = lane / 4 % 4, m = lane / 16; a wave holds 32 dims of all keys)
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const int r = lane & 15, m = lane >> 4, kg = lane & 3, vc = (lane >> 2) & 3;
+    u32x4 kv[2], vv[2];
+    int kk[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      kk[i] = 8 * (r >> 2) + 4 * i + (r & 3);
+      kv[i] = vv[i] = zero;
+      if (kk[i] >= klo && kk[i] < nkeys)
+        kv[i] = ldg128(p.k_new + ((int64_t)(tk0 + kk[i]) * hkv + g) * kHeadDim + 32 * wave + 8 * m);
+      const int vk = 8 * kg + 4 * i + m;
+      if (vk >= klo && vk < nkeys)
+        vv[i] = ldg128(p.v_new + ((int64_t)(tk0 + vk) * hkv + g) * kHeadDim + 32 * wave + 8 * vc);
+    }
+    // a run lies on one page (PG >= 32) or on two (PG = 16); both pools put a
+    // block (and a 16-key page-head) at the same element offset
+    const int lp = (int)(base >> pv.pg_shift);
+    const int page0 = base >= 0 ? uniform_page(pv, rb, lp) : -1;
+    const int page1 = two && base >= 0 && nkeys > 16 ? uniform_page(pv, rb, lp + 1) : page0;
+    const int64_t boff = (int64_t)((int)base & (pg - 1)) << kHeadDimShift;  // the run's block in its page
+    const int64_t off0 = ((((int64_t)page0 * hkv + g) << pv.pg_shift) << kHeadDimShift) + (two ? 0 : boff);
+    const int64_t off1 = two ? (((int64_t)page1 * hkv + g) << pv.pg_shift) << kHeadDimShift : off0;
+    const bool ok0 = page0 >= 0, ok1 = page1 >= 0;
+    {
+      const bool second = two && r >= 8;
+      uint16_t *dst = pv.k_pool + (second ? off1 : off0) + ((((4 * wave + m) << (pv.vb_shift - 1)) + (two ? r & 7 : r)) << 3);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)  // halves: 16 16-byte pieces x B / 2 rows apart
+        if (kk[i] >= klo && kk[i] < nkeys && (second ? ok1 : ok0)) stg128(dst + ((i << 6) << pv.vb_shift), kv[i]);
+    }
+    // lane m holds dims 2 m, 2 m + 1 of keys 8 kg .. +7 after the transposes
+    uint32_t w[8];
+    transpose4(vv[0], w);
+    transpose4(vv[1], w + 4);
+    u32x4 lo, hi;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      lo[q] = __builtin_amdgcn_perm(w[2 * q + 1], w[2 * q], 0x05040100u);
+      hi[q] = __builtin_amdgcn_perm(w[2 * q + 1], w[2 * q], 0x07060302u);
+    }
+    const bool second = two && kg >= 2;
+    if (second ? ok1 : ok0) {
+      const uint32_t bits = key_range_bits(8 * kg, klo, nkeys - 1);
+      uint16_t *dst = pv.v_pool + (second ? off1 : off0) + ((32 * wave + 8 * vc + 2 * m) << pv.vb_shift) +
+                      8 * (two ? kg & 1 : kg);
+      uint16_t *dst1 = dst + (1 << pv.vb_shift);  // the next dim
+      if (bits == 0xFFu) {
+        stg128(dst, lo);
+        stg128(dst1, hi);
+      } else if (bits != 0u) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          if ((bits >> e) & 1u) {
+            dst[e] = (uint16_t)(lo[e >> 1] >> (16 * (e & 1)));
+            dst1[e] = (uint16_t)(hi[e >> 1] >> (16 * (e & 1)));
+          }
+        }
+      }
     }
   }
 }
@@ -134,8 +292,22 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
 
 hipError_t launch_kv_append(const AppendParams &p, hipStream_t stream) {
   if (p.total_tokens <= 0) return hipSuccess;
-  const int blocks = (p.total_tokens + kTokPerBlock - 1) / kTokPerBlock;
-  return launch_kernel(kv_append_kernel, dim3(blocks, p.hkv), dim3(kThreads), stream, p);
+  // Chunks: 32-token tiles, a run each. A few tokens per sequence (decode
+  // steps), or a few in all, are bound by the launch and a chain of loads:
+  // 8-token tiles, scattered, put them on more compute units with the rows'
+  // loads ahead of the slots (8 heads, replayed as a graph, us per call, runs
+  // against scatter: 16 sequences x 16 tokens 5.2 / 3.8, 1 x 100 4.7 / 3.7,
+  // 32 x 12 8.0 / 6.0, 1 x 300 4.8 / 5.2, 4 x 2048 into a ring 6.1 / 12,
+  // 300 x 24 23 / 42, 300 x 100 68 / 200).
+  // (The grid counts fewer than 2^32 threads: inputs of 2^27 token-heads, 69 GB
+  // and more, take the 32-token tiles whatever their lengths.)
+  const bool chunks = !p.ctx_lens && ((p.total_tokens > 256 && p.total_tokens / 16 >= p.ns) ||
+                                      (int64_t)p.total_tokens * p.hkv >= (1 << 27));
+  const int tok = chunks ? kRun : 8;
+  const int64_t tiles = ((int64_t)p.total_tokens + tok - 1) / tok;
+  const dim3 grid((unsigned)(tiles * p.hkv));
+  return chunks ? launch_kernel(kv_append_kernel<kRun>, grid, dim3(kThreads), stream, p)
+                : launch_kernel(kv_append_kernel<8>, grid, dim3(kThreads), stream, p);
 }
 
 }  // namespace hswa

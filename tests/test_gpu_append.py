@@ -75,3 +75,43 @@ def test_append_empty_and_noop(gpu_lib):
                    torch.tensor([0], dtype=torch.int32, device="cuda"))
     torch.cuda.synchronize()
     assert np.array_equal(before, to_bits(kv.k_pool))
+
+
+# Runs of 32 positions, their edges, and sequences on both sides of the lengths
+# that are scattered token by token: (kind, window, page size, Hkv, [(start, count)] per sequence)
+RUN_CASES = [
+    # all counts around 8 and 32 from every alignment of a 16-byte piece
+    ("full", 0, 16, 2, [(3 * i, c) for i, c in enumerate([7, 8, 9, 31, 32, 33, 63, 64, 65, 97, 1, 200])]),
+    ("full", 0, 32, 1, [(5 + 7 * i, c) for i, c in enumerate([33, 32, 31, 64, 96, 100, 1, 2, 300])]),
+    ("full", 0, 128, 3, [(8 * i, c) for i, c in enumerate([40, 8, 9, 500, 129])]),
+    # long chunks next to single decode tokens in one call (a mixed step)
+    ("full", 0, 64, 2, [(100, 1000)] + [(17 * i, 1) for i in range(40)] + [(31, 333)]),
+    # short appends only: the 8-token tiles, with sequences of up to 31 tokens
+    ("full", 0, 64, 4, [(11 * i, 1 + i % 31) for i in range(50)]),
+    # rings: the call evicts its own first tokens, or keeps them all
+    ("swa", 128, 16, 1, [(0, 700), (37, 150), (5, 9), (500, 161)]),
+    ("swa", 33, 32, 2, [(0, 95), (1, 96), (2, 97), (3, 1), (64, 64)]),
+    # more sequences than the LDS copy of cu_seqlens holds
+    ("full", 0, 16, 1, [(i % 16, 1 + (i % 500 == 0) * 40) for i in range(4100)]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(RUN_CASES)))
+def test_append_runs_bit_exact(gpu_lib, case):
+    kind, window, pg, hkv, seqs = RUN_CASES[case]
+    print(f"[append-runs] case={case} kind={kind} W={window} PG={pg} Hkv={hkv} ns={len(seqs)}", flush=True)
+    shape = hswa.Shape(hkv, hkv, 128, pg)
+    starts = [s for s, _ in seqs]
+    final = [s + c for s, c in seqs]
+    layer, kv = make_layer(kind, window, shape, final, (101, case))
+    hist = SeqHistory(final, hkv, 128, 101, case)
+    exp_k, exp_v = to_bits(kv.k_pool), to_bits(kv.v_pool)
+    slots = append_history(layer, shape, kv, hist, starts, final)
+    exp_slots = OL.slot_mapping(OL.SWA if kind == "swa" else OL.FULL, window or None, pg, kv.table_host, starts,
+                                [c for _, c in seqs])
+    assert np.array_equal(slots, exp_slots), "slot mapping differs from the oracle"
+    kn = np.concatenate([hist.k[b][s:s + c] for b, (s, c) in enumerate(seqs)])
+    vn = np.concatenate([hist.v[b][s:s + c] for b, (s, c) in enumerate(seqs)])
+    exp_k, exp_v = OL.apply_append(exp_k, exp_v, exp_slots, kn, vn)
+    torch.cuda.synchronize()
+    _check_pools(kv, exp_k, exp_v)
