@@ -38,9 +38,7 @@ namespace hswa {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kRows = 256;  // query rows per workgroup
 constexpr int kKT = 64;     // keys per tile
-constexpr int kCG = 2;      // 16-column MFMA groups per wave
 constexpr int kXcds = 8;
 constexpr int kBufs = 4;  // LDS tile buffers (a power of two): two being read, one stored, one loading
 static_assert((kBufs & (kBufs - 1)) == 0, "buffer indices are taken modulo kBufs with a mask");
@@ -69,18 +67,6 @@ __device__ __forceinline__ uint32_t v_lds_off(int h, int q, int d) {
   return (uint32_t)(kKTileBytes + ((8 * h + (d >> 4)) * 64 + (d & 15) + 16 * q) * 16);
 }
 
-__device__ __forceinline__ int64_t prefix_page(const PoolView &pv, int b, int key, bool &ok) {
-  int lp = key >> pv.pg_shift;
-  if (pv.ring > 0) lp %= pv.ring;
-  if (lp >= pv.stride) {
-    ok = false;
-    return 0;
-  }
-  const int64_t page = pv.table[(int64_t)b * pv.stride + lp];
-  ok = page >= 0 && page < pv.num_pages;
-  return ok ? page : 0;
-}
-
 constexpr int kStage = kKT * kHeadDim / 8 / kThreads;  // 16-byte pieces per thread per tile (K or V)
 static_assert(kStage == 2 && kKT == 64, "V staging maps piece i of a thread to 32-key block i");
 
@@ -93,23 +79,20 @@ static_assert(kStage == 2 && kKT == 64, "V staging maps piece i of a thread to 3
 // block i (a wave reads one contiguous 1 KiB of the block).
 // K tile pieces in pool order: piece idx (0 .. 1023) is 16-byte piece idx & 511
 // of the tile's 32-key block idx >> 9 (half (idx >> 8) & 1, slab (idx >> 6) & 3,
-// dim piece (idx >> 4) & 3, row idx & 15 of the block's K layout), i.e. dims
-// 8 k_piece_c .. +7 of tile key k_piece_key. LDS holds it at byte 16 idx.
-__device__ __forceinline__ int k_piece_key(int idx) {
-  const int r = idx & 15;
-  return ((idx >> 9) << 5) | ((r >> 2) << 3) | (((idx >> 8) & 1) << 2) | (r & 3);
-}
-__device__ __forceinline__ int k_piece_c(int idx) { return ((idx >> 6) & 3) * 4 + ((idx >> 4) & 3); }
-
+// dim piece (idx >> 4) & 3, row idx & 15 of the block's K layout). LDS holds it
+// at byte 16 idx.
 __device__ __forceinline__ int v_piece_dim(int tid) { return 16 * (tid >> 6) + (tid & 15); }
-__device__ __forceinline__ int v_piece_keys(int tid, int i) { return 4 * i + ((tid >> 4) & 3); }
 
 struct Stage {
   u32x4 k[kStage], v[kStage];
   bool vrow;  // chunk tile: k[] holds key rows, v[] pieces follow the chunk mapping
 };
 
+// kCG: 16-column MFMA groups per wave, 128 kCG query rows per workgroup.
+// kPage: keys of a page, 64 standing for 64 and more.
+template <int kCG, int kPage>
 __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
+  constexpr int kRows = 8 * 16 * kCG;
   // kBufs tile buffers, each a K tile then a V^T tile (byte offsets below)
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[kBufs * kBufBytes];
 
@@ -173,68 +156,18 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     }
   }
 
+  // ---- the key range in tiles ----
+  // Cut at P: tiles of cached keys, aligned to 64 absolute positions (so that a
+  // tile is whole pool blocks), then tiles of the chunk's own keys, aligned to
+  // P. No tile holds both kinds; a tile at an end of its range is partly masked.
+  const int kt0 = klo & ~(kKT - 1);
+  const int ncached = klo < P ? ((P - 1) >> 6) - (klo >> 6) + 1 : 0;
+  const int nlo = max(klo, P);  // first new key in range
+  const int ntiles = ncached + ((khi - P) >> 6) - ((nlo - P) >> 6) + 1;
+  const int ktn = P + ((nlo - P) & ~(kKT - 1)) - kKT * ncached;  // tile j >= ncached starts at ktn + 64 j
+  auto tile_key = [&](int j) { return kKT * j + (j < ncached ? kt0 : ktn); };
+
   // ---- staging: global -> registers -> LDS ----
-  const bool page_tiles = shift >= 6;  // PG >= 64: a 64-key tile lies on one page
-  // General tile (range ends, the prefix / chunk boundary, PG < 64): per-key
-  // source and range checks. With PG >= 64 the tile's page (tpage, from the
-  // lane table) serves every cached key; otherwise each key looks its page up.
-  auto cached_page = [&](int j, int tpage, bool &ok) -> int64_t {
-    if (page_tiles) {
-      ok = tpage >= 0;
-      return ok ? tpage : 0;
-    }
-    return prefix_page(pv, b, j, ok);
-  };
-  auto load_tile = [&](int kt, int tpage, Stage &st) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      const int idx = tid + kThreads * i;
-      const int c = k_piece_c(idx);
-      const int j = kt + k_piece_key(idx);
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (j >= klo && j <= khi) {
-        if (j < P) {
-          bool ok;
-          const int64_t page = cached_page(j, tpage, ok);
-          if (ok) v = ldg128(pv.k_pool + k_offset(pv, page, hkv, g, j & (pg - 1), c * 8));
-        } else {
-          v = ldg128(p.k_new + ((int64_t)(tok0 + j - P) * hkv + g) * kHeadDim + c * 8);
-        }
-      }
-      st.k[i] = v;
-    }
-#pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      const int d = v_piece_dim(tid), kc = v_piece_keys(tid, i);
-      const int j0 = kt + 8 * kc;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (j0 >= klo && j0 + 7 <= khi && j0 + 7 < P) {
-        bool ok;
-        const int64_t page = cached_page(j0, tpage, ok);
-        if (ok) v = ldg128(pv.v_pool + v_offset(pv, page, hkv, g, j0 & (pg - 1), d));
-      } else if (j0 + 7 >= klo && j0 <= khi) {
-        uint32_t e[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int j = j0 + t;
-          e[t] = 0u;
-          if (j >= klo && j <= khi) {
-            if (j < P) {
-              bool ok;
-              const int64_t page = cached_page(j, tpage, ok);
-              if (ok) e[t] = pv.v_pool[v_offset(pv, page, hkv, g, j & (pg - 1), d)];
-            } else {
-              e[t] = p.v_new[((int64_t)(tok0 + j - P) * hkv + g) * kHeadDim + d];
-            }
-          }
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = e[2 * t] | (e[2 * t + 1] << 16);
-      }
-      st.v[i] = v;
-    }
-    st.vrow = false;
-  };
   // Chunk tile: every key is one of this chunk's own (key >= P). K and V rows
   // are 256-byte runs of k_new / v_new, loaded as 16-byte pieces of a row. K
   // piece i of lane l of wave w is MFMA row l % 16 of K block (h = i,
@@ -248,7 +181,7 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
 #pragma unroll
     for (int i = 0; i < kStage; ++i) {
       const int j = kt + 32 * i + 8 * (r >> 2) + 4 * ab + (r & 3);
-      const bool in = j >= klo && j <= khi;
+      const bool in = j >= nlo && j <= khi;
       const int c = 4 * (wave & 3) + (lane >> 4);
       const int64_t off = ((int64_t)(tok0 + (in ? j - P : 0)) * hkv + g) * kHeadDim + c * 8;
       st.k[i] = in ? ldg128(p.k_new + off) : z;
@@ -256,7 +189,7 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
 #pragma unroll
     for (int i = 0; i < kStage; ++i) {
       const int j = kt + 8 * wave + 4 * i + (lane >> 4);
-      const bool in = j >= klo && j <= khi;
+      const bool in = j >= nlo && j <= khi;
       const int64_t off = ((int64_t)(tok0 + (in ? j - P : 0)) * hkv + g) * kHeadDim + (lane & 15) * 8;
       st.v[i] = in ? ldg128(p.v_new + off) : z;
     }
@@ -291,43 +224,117 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     }
     st.vrow = true;
   };
-  // Interior tile: every key cached, in range and (PG >= 64) on one page whose
-  // id was fetched ahead; the K tile is two 8 KiB K blocks and the V tile two
-  // [D][32] blocks of 8 KiB, all contiguous: plain 16-byte loads, consecutive
-  // threads at consecutive addresses.
-  // The tile's two base addresses are wave-uniform (scalar registers) and each
-  // load adds a fixed 32-bit per-lane byte offset (buffer loads), so a tile's
-  // loads need no vector address arithmetic.
+  // Page ids of cached tiles come from a per-wave window of the block table:
+  // lane i holds the entry of logical page tab_lp0 + i, and a tile's ids are
+  // read with v_readlane. The next window is loaded when one is entered, 16 to
+  // 64 tiles before its first use, so no tile waits for the table. (Entries are
+  // checked where they are used; -1 past the cached pages.)
+  int tab_page = -1, tab_next = -1, tab_lp0 = kt0 >> shift;
+  auto load_tab = [&](int lp0) {
+    const int lp = lp0 + lane;
+    int v = -1;
+    if (lp <= ((P - 1) >> shift) && P > 0) {
+      const int e = pv.ring > 0 ? lp % pv.ring : lp;
+      if (e < pv.stride) v = pv.table[(int64_t)b * pv.stride + e];
+    }
+    return v;
+  };
+  if (ncached > 0) {
+    tab_page = load_tab(tab_lp0);
+    tab_next = load_tab(tab_lp0 + kWave);
+  }
+  auto page_at = [&](int lp) {  // -1: not a valid page
+    const int v = __builtin_amdgcn_readlane(tab_page, lp - tab_lp0);
+    return v >= 0 && v < pv.num_pages ? v : -1;
+  };
+  // Cached tile: the K tile is two 8 KiB K blocks and the V tile two [D][32]
+  // blocks of 8 KiB (16-key pages: four 4 KiB blocks each), contiguous in the
+  // pools. The base addresses are wave-uniform (scalar registers) and each load
+  // adds a fixed 32-bit per-lane byte offset (buffer loads), so a tile's loads
+  // need no vector address arithmetic; with 16-key pages a lane chooses one of
+  // a block's two pages (three vector instructions a load). Looking a page up
+  // per key instead, with 2-byte V loads where a piece crossed a range end, took
+  // a PG 16 call of 4 ragged chunks (3263 tokens over 463-2957 cached, 32 / 8
+  // heads) 232 us against 150, and 4 x 2048 over 8192 (64 / 8) 3239 against
+  // 2104 (1965 with PG 64).
   // (The empty asm keeps the offsets opaque: the compiler would otherwise fold
   // the constant 8 KiB step between a thread's two pieces into arithmetic of
   // its own.)
-  uint32_t pg_koff[kStage] = {(uint32_t)tid * 16u, (uint32_t)(tid + kThreads) * 16u};
-  uint32_t pg_voff[kStage] = {(uint32_t)(v_piece_dim(tid) * 32 + ((tid >> 4) & 3) * 8) * 2u,
-                              (uint32_t)(32 * kHeadDim + v_piece_dim(tid) * 32 + ((tid >> 4) & 3) * 8) * 2u};
+  constexpr int kPages = kKT / kPage;  // pages of a tile
+  const int vq = (tid >> 4) & 3;       // V^T piece: keys 8 vq .. +7 of its 32-key block
+  uint32_t pg_koff[kStage], pg_voff[kStage];
 #pragma unroll
-  for (int i = 0; i < kStage; ++i) asm volatile("" : "+v"(pg_koff[i]), "+v"(pg_voff[i]));
-  // For a tile on one page (PG >= 64, in-page offset a multiple of 64) both
-  // pools put the page-head at the same byte offset, page * (Hkv PG D 2) +
+  for (int i = 0; i < kStage; ++i) {
+    if constexpr (kPage == 16) {
+      pg_koff[i] = (uint32_t)((tid >> 4) * 128 + (tid & 7) * 16);  // 8-row slabs
+      pg_voff[i] = (uint32_t)(v_piece_dim(tid) * 32 + (vq & 1) * 16);
+    } else {
+      const uint32_t blk = kPage == 32 ? 0u : 8192u * i;  // PG >= 64: both blocks from one base
+      pg_koff[i] = blk + (uint32_t)tid * 16u;
+      pg_voff[i] = blk + (uint32_t)(v_piece_dim(tid) * 32 + vq * 8) * 2u;
+    }
+    asm volatile("" : "+v"(pg_koff[i]), "+v"(pg_voff[i]));
+  }
+  // Both pools put a page-head at the same byte offset, page * (Hkv PG D 2) +
   // g * (PG D 2), and its 32-key blocks 8 KiB apart: one scalar offset serves
   // the K and the V loads.
   const uint32_t page_bytes = (uint32_t)hkv << (shift + kHeadDimShift + 1);
   const uint64_t head_bytes = (uint64_t)g << (shift + kHeadDimShift + 1);
-  auto load_tile_page = [&](int kt, int page, Stage &st) __attribute__((always_inline)) {
-    const uint64_t o = (uint64_t)(uint32_t)max(page, 0) * page_bytes + head_bytes +
-                       (uint64_t)(((uint32_t)kt & (uint32_t)(pg - 1)) >> 5) * 8192u;
-    const char *kbase = reinterpret_cast<const char *>(pv.k_pool) + o;
-    const char *vbase = reinterpret_cast<const char *>(pv.v_pool) + o;
-    // buffer loads: the tile's 16 KiB from a scalar resource on its first
-    // byte plus this lane's fixed 32-bit offset, so a tile's four loads need
-    // no vector address arithmetic (offsets past the 16 KiB would read 0)
-    const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(kbase), 0, kKTileBytes, kBufferWord3);
-    const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(vbase), 0, kKTileBytes, kBufferWord3);
+  auto page_off = [&](int kt, int page) {
+    uint64_t o = (uint64_t)(uint32_t)max(page, 0) * page_bytes + head_bytes;
+    if constexpr (kPage == 64) o += (uint64_t)(((uint32_t)kt & (uint32_t)(pg - 1)) >> 5) * 8192u;
+    return o;
+  };
+  auto buf_load = [&](uint16_t *pool, uint64_t o, int bytes, uint32_t off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char *>(pool) + o, 0, bytes, kBufferWord3), (int)off, 0, 0));
+  };
+  auto load_tile_cached = [&](int kt, Stage &st) __attribute__((always_inline)) {
+    const int lp = kt >> shift;
+    if (lp - tab_lp0 >= kWave) {
+      tab_lp0 += kWave;
+      tab_page = tab_next;
+      tab_next = load_tab(tab_lp0 + kWave);
+    }
+    int page[kPages];
+    bool whole = kt >= klo && kt + kKT <= P;
 #pragma unroll
-    for (int i = 0; i < kStage; ++i) {
-      st.k[i] = __builtin_amdgcn_raw_buffer_load_b128(krs, (int)pg_koff[i], 0, 0);
-      st.v[i] = __builtin_amdgcn_raw_buffer_load_b128(vrs, (int)pg_voff[i], 0, 0);
+    for (int n = 0; n < kPages; ++n) {
+      page[n] = page_at(lp + n);
+      whole = whole && page[n] >= 0;
     }
     st.vrow = false;
+    // 16-key pages: the page of this lane's K rows (8 (r >> 3) ..) and V keys
+    const bool ksel = kPage == 16 && (tid & 8), vsel = kPage == 16 && (vq & 2);
+    if (whole) {
+#pragma unroll
+      for (int i = 0; i < kStage; ++i) {
+        if constexpr (kPage == 16) {
+          const uint64_t o0 = page_off(kt, page[2 * i]), o1 = page_off(kt, page[2 * i + 1]);
+          st.k[i] = ldg128_global(reinterpret_cast<const char *>(pv.k_pool) + (ksel ? o1 : o0) + pg_koff[i]);
+          st.v[i] = ldg128_global(reinterpret_cast<const char *>(pv.v_pool) + (vsel ? o1 : o0) + pg_voff[i]);
+        } else {
+          const uint64_t o = page_off(kt, page[kPage == 32 ? i : 0]);
+          st.k[i] = buf_load(pv.k_pool, o, kKTileBytes, pg_koff[i]);
+          st.v[i] = buf_load(pv.v_pool, o, kKTileBytes, pg_voff[i]);
+        }
+      }
+      return;
+    }
+    // A tile that crosses an end of the cached range (its out-of-range V is
+    // zeroed: those slots may hold anything, NaN included, and meet probability
+    // 0; their K only reaches masked scores) or meets an invalid page (a zero
+    // key and value).
+#pragma unroll
+    for (int i = 0; i < kStage; ++i) {
+      const int n0 = kPage == 16 ? 2 * i : kPage == 32 ? i : 0, n1 = kPage == 16 ? 2 * i + 1 : n0;
+      const int kpage = ksel ? page[n1] : page[n0], vpage = vsel ? page[n1] : page[n0];
+      u32x4 k = {0u, 0u, 0u, 0u}, v = k;
+      if (kpage >= 0) k = ldg128(reinterpret_cast<const char *>(pv.k_pool) + page_off(kt, kpage) + pg_koff[i]);
+      if (vpage >= 0) v = ldg128(reinterpret_cast<const char *>(pv.v_pool) + page_off(kt, vpage) + pg_voff[i]);
+      st.k[i] = k;
+      st.v[i] = keep_bf16x8(v, key_range_bits(kt + 32 * i + 8 * vq, klo, P - 1));
+    }
   };
   // LDS addresses are a per-lane byte offset (fixed for the kernel) plus the
   // buffer's byte offset (a scalar), with everything else in the instruction's
@@ -391,49 +398,11 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     for (int dt = 0; dt < 8; ++dt) acc[cg][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  // One 64-key tile, processed as two 32-key halves (QK^T, softmax, PV each),
-  // which keeps the score and probability registers of a wave at 32 + 16.
-  // ---- pipelined tile loop ----
-  // Work is split into half tiles of 32 keys. The QK^T of the next half is
-  // issued before the softmax of the current one, so the matrix cores and the
-  // VALU work of a wave can overlap; LDS holds three tiles (the two being read
-  // and the one being written), with one barrier per tile.
-  const int kt0 = klo & ~(kKT - 1);
-  const int ntiles = (khi - kt0) / kKT + 1;
-  // A tile is "interior" when all of its keys are cached, inside [klo, khi]
-  // and (PG >= 64) on a single page; its page id is looked up one tile ahead.
-  auto interior = [&](int kt) { return page_tiles && kt >= klo && kt + kKT - 1 <= khi && kt + kKT - 1 < P; };
-  // Page ids of interior tiles come from a per-wave window of the block table:
-  // lane i holds the physical page of logical page tab_lp0 + i, refilled every
-  // 64 pages, and a tile's id is read with v_readlane (no per-tile memory
-  // round trip). -1 marks a tile that is not interior or whose page is invalid.
-  int tab_page = -1, tab_lp0 = -(1 << 30);
-  // For PG >= 64 every 64-key tile lies on one logical page: its physical page
-  // comes from the lane table for any tile that starts in the cached prefix
-  // (-1 for a chunk tile or a page that is not valid).
-  auto tile_page = [&](int kt) {
-    if (!page_tiles || kt >= P) return -1;
-    const int lp = kt >> shift;
-    if (lp - tab_lp0 >= kWave || lp < tab_lp0) {
-      tab_lp0 = lp;
-      const int lpl = lp + lane;
-      int page = -1;
-      if (lpl <= ((P - 1) >> shift)) {
-        const int e = pv.ring > 0 ? lpl % pv.ring : lpl;
-        if (e < pv.stride) {
-          const int64_t v = pv.table[(int64_t)b * pv.stride + e];
-          page = (v >= 0 && v < pv.num_pages) ? (int)v : -1;
-        }
-      }
-      tab_page = page;
-    }
-    return __builtin_amdgcn_readlane(tab_page, lp - tab_lp0);
-  };
-  auto fetch = [&](int kt, int page, Stage &st) __attribute__((always_inline)) {
-    if (page >= 0 && interior(kt)) load_tile_page(kt, page, st);
-    else if (kt >= P && chunk_buf && kt >= klo && kt + kKT - 1 <= khi) load_tile_chunk_full(kt, st);
-    else if (kt >= P) load_tile_chunk(kt, st);
-    else load_tile(kt, page, st);
+  auto fetch = [&](int j, Stage &st) __attribute__((always_inline)) {
+    const int kt = tile_key(j);
+    if (j < ncached) load_tile_cached(kt, st);
+    else if (chunk_buf && kt >= nlo && kt + kKT - 1 <= khi) load_tile_chunk_full(kt, st);
+    else load_tile_chunk(kt, st);
   };
 
   // QK^T of one half tile: S^T for keys kt + 32h .. +31.
@@ -456,8 +425,9 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
       }
     }
   };
-  // Per-element mask of a half tile on the diagonal, window edge or range ends.
-  auto mask_half = [&](int kt, int h, f32x4 (&sc)[2][kCG]) {
+  // Per-element mask of a half tile on the diagonal, window edge or range ends
+  // (kend: the last key of the tile's kind, P - 1 or khi).
+  auto mask_half = [&](int kt, int kend, int h, f32x4 (&sc)[2][kCG]) {
     // this lane's 8 keys are kt + 32h + 8q + e, e = 4 ab + i; allowed e form
     // the interval [lo_e, hi_e] of the column's visible keys
     // kt laundered: the per-lane bounds below are then formed here, in the
@@ -468,8 +438,8 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     const int j0 = ktl + 32 * h + 8 * q;
 #pragma unroll
     for (int cg = 0; cg < kCG; ++cg) {
-      const int lo_e = max(max(clo[cg], klo) - j0, 0);
-      const int hi_e = min(min(cpos[cg], khi) - j0, 7);
+      const int lo_e = max(clo[cg] - j0, 0);
+      const int hi_e = min(min(cpos[cg], kend) - j0, 7);
       const uint32_t bits = hi_e < lo_e ? 0u : ((2u << hi_e) - 1u) & ~((1u << lo_e) - 1u);
 #pragma unroll
       for (int ab = 0; ab < 2; ++ab)
@@ -477,8 +447,8 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
         for (int i = 0; i < 4; ++i) sc[ab][cg][i] = (bits >> (4 * ab + i)) & 1u ? sc[ab][cg][i] : -INFINITY;
     }
   };
-  auto needs_mask = [&](int kt) {
-    return kt + kKT - 1 > pfirst || kt < klo || kt + kKT - 1 > khi || (W > 0 && kt < plast - W + 1);
+  auto needs_mask = [&](int j, int kt) {
+    return kt + kKT > (j < ncached ? P : pfirst + 1) || (W > 0 && kt < plast - W + 1);
   };
   // Lazy raise of the running maximum, checked after the fact. The
   // exponentials of a tile are taken against the running maximum m as it
@@ -576,13 +546,13 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
   };
 
   Stage st;
-  fetch(kt0, tile_page(kt0), st);
+  fetch(0, st);
   store_tile(0, st);
   if (ntiles > 1) {
-    fetch(kt0 + kKT, tile_page(kt0 + kKT), st);
+    fetch(1, st);
     store_tile(1, st);
   }
-  if (ntiles > 2) fetch(kt0 + 2 * kKT, tile_page(kt0 + 2 * kKT), st);
+  if (ntiles > 2) fetch(2, st);
   __syncthreads();
   const bool lag = wave >= kThreads / kWave / 2;  // group B
 
@@ -602,9 +572,10 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
 #pragma unroll
       for (int i = 0; i < 16 - kAhead; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, kCG, 0);
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * kAhead, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, kCG * kAhead, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
     qk_half(buf, 0, sc[0]);
     qk_half(buf, 1, sc[1]);
@@ -612,21 +583,22 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
 #pragma unroll
     for (int i = 0; i < 16 - kAhead; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 1);
+      __builtin_amdgcn_sched_group_barrier(0x008, kCG, 1);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kAhead, 1);
+    __builtin_amdgcn_sched_group_barrier(0x008, kCG * kAhead, 1);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(0);
   };
   // softmax phase of tile jt, with this thread's share of the staging: tile
   // jt+2 from registers to LDS, tile jt+3's global loads
   auto softmax_phase = [&](int jt) __attribute__((always_inline)) {
-    const int kt = kt0 + jt * kKT;
+    const int kt = tile_key(jt);
     if (jt + 2 < ntiles) store_tile((jt + 2) & (kBufs - 1), st);
-    if (jt + 3 < ntiles) fetch(kt + 3 * kKT, tile_page(kt + 3 * kKT), st);
-    if (needs_mask(kt)) {
-      mask_half(kt, 0, sc[0]);
-      mask_half(kt, 1, sc[1]);
+    if (jt + 3 < ntiles) fetch(jt + 3, st);
+    if (needs_mask(jt, kt)) {
+      const int kend = jt < ncached ? P - 1 : khi;
+      mask_half(kt, kend, 0, sc[0]);
+      mask_half(kt, kend, 1, sc[1]);
     }
     softmax_tile(sc, pf);
   };
@@ -681,15 +653,24 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
 
 }  // namespace
 
+template <int kCG>
+hipError_t launch_prefill_rows(const PrefillParams &p, hipStream_t stream) {
+  const int npos = 128 * kCG / p.group;
+  const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
+  const int64_t pairs_per_xcd = ((int64_t)p.ns * p.hkv + kXcds - 1) / kXcds;
+  const dim3 grid((unsigned)(pairs_per_xcd * ntq * kXcds)), block(kThreads);
+  switch (p.pool.pg_shift) {
+    case 4: return launch_kernel(prefill_kernel<kCG, 16>, grid, block, stream, p);
+    case 5: return launch_kernel(prefill_kernel<kCG, 32>, grid, block, stream, p);
+    default: return launch_kernel(prefill_kernel<kCG, 64>, grid, block, stream, p);
+  }
+}
+
 hipError_t launch_prefill(const PrefillParams &p, hipStream_t stream) {
   if (p.ns <= 0 || p.max_chunk_len <= 0 || p.total_tokens <= 0) return hipSuccess;
   if (p.pool.window > 0 && prefill_run_fits(p)) return launch_prefill_run(p, stream);
   if (p.pool.window > 0 && p.pool.window <= kPrefillWindowMax) return launch_prefill_window(p, stream);
-  const int npos = kRows / p.group;
-  const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
-  const int64_t pairs_per_xcd = ((int64_t)p.ns * p.hkv + kXcds - 1) / kXcds;
-  const int64_t grid = pairs_per_xcd * ntq * kXcds;
-  return launch_kernel(prefill_kernel, dim3((unsigned)grid), dim3(kThreads), stream, p);
+  return launch_prefill_rows<2>(p, stream);
 }
 
 }  // namespace hswa

@@ -117,3 +117,65 @@ def test_prefill_window_kernel_boundaries(gpu_lib, hq, hkv, window):
         gpu, ref, _ = run_prefill("swa", window, pg, hq, hkv, [0, 37, 300, 1000], [700, 333, 64, 900],
                                   (305, hq, window, pg))
         assert_close(gpu, ref, f"prefill W={window} hq={hq} hkv={hkv} PG={pg}")
+
+
+# Tiles of cached keys over every page class: prefixes around tile, page and
+# block-table-window edges (64 table entries: 1024 keys of 16-key pages, 2048 of
+# 32-key ones), a window past the windowed kernels' range with a ring and with
+# released pages: (page size, window, prefix, chunk)
+CACHED_TILE_CASES = [
+    (16, 0, 1, 70), (16, 0, 15, 3), (16, 0, 63, 130), (16, 0, 64, 64), (16, 0, 65, 1), (16, 0, 1023, 20),
+    (16, 0, 1040, 90), (16, 0, 2113, 33), (32, 0, 31, 65), (32, 0, 33, 64), (32, 0, 2047, 40), (32, 0, 4200, 17),
+    (64, 0, 63, 129), (64, 0, 4097, 30), (128, 0, 130, 100), (256, 0, 300, 64), (16, 600, 1700, 100),
+    (32, 700, 2500, 80), (64, 513, 1111, 200), (128, 1000, 1500, 65),
+]
+
+
+@pytest.mark.parametrize("pg,window,prefix,chunk", CACHED_TILE_CASES)
+def test_prefill_cached_tiles(gpu_lib, pg, window, prefix, chunk):
+    print(f"[prefill-tiles] PG={pg} W={window} P={prefix} C={chunk}", flush=True)
+    hq, hkv, d = 8, 2, 128
+    shape = hswa.Shape(hq, hkv, d, pg)
+    lens = [prefix, max(0, prefix - 17)]
+    final = [p + chunk for p in lens]
+    kind = "swa" if window else "full"
+    layer, kv = make_layer(kind, window, shape, final, (203, pg, prefix))  # NaN in every unused slot
+    hist = SeqHistory(final, hkv, d, 203, pg, prefix)
+    append_history(layer, shape, kv, hist, [0, 0], lens)
+    qb = synth.normal_bf16((2 * chunk, hq, d), 203, pg, prefix, synth.TAG_Q)
+    kn = np.concatenate([hist.k[b][p:] for b, p in enumerate(lens)])
+    vn = np.concatenate([hist.v[b][p:] for b, p in enumerate(lens)])
+    out = torch.full((2 * chunk, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hswa.prefill(layer, shape, kv.cache, to_dev(qb), to_dev(kn), to_dev(vn), i32([0, chunk, 2 * chunk]), i32(lens),
+                 chunk, out)
+    torch.cuda.synchronize()
+    gpu, qf = to_f64(out), OA.bf16_bits_to_f64(qb)
+    for b, p in enumerate(lens):
+        ref = OA.prefill(qf[b * chunk:(b + 1) * chunk], OA.bf16_bits_to_f64(hist.k[b]),
+                         OA.bf16_bits_to_f64(hist.v[b]), p, window or None)
+        assert_close(gpu[b * chunk:(b + 1) * chunk], ref, f"PG {pg} W {window} P {p}")
+
+
+@pytest.mark.parametrize("pg", [16, 32, 64])
+def test_prefill_invalid_page_reads_as_zero(gpu_lib, pg):
+    """A cached page whose table entry is invalid counts as zero keys and values."""
+    print(f"[prefill-invalid] PG={pg}", flush=True)
+    hq, hkv, d, prefix, chunk = 8, 2, 128, 200, 40
+    shape = hswa.Shape(hq, hkv, d, pg)
+    layer, kv = make_layer("full", 0, shape, [prefix + chunk], (204, pg))
+    hist = SeqHistory([prefix + chunk], hkv, d, 204, pg)
+    append_history(layer, shape, kv, hist, [0], [prefix])
+    qb = synth.normal_bf16((chunk, hq, d), 204, pg, synth.TAG_Q)
+    kf, vf = OA.bf16_bits_to_f64(hist.k[0]), OA.bf16_bits_to_f64(hist.v[0])
+    for entry, bad in ((1, -1), (192 // pg, kv.num_pages)):  # a whole tile's page, and the last (partial) tile's
+        saved = int(kv.block_table[0, entry])
+        kv.block_table[0, entry] = bad
+        k, v = kf.copy(), vf.copy()
+        k[entry * pg:min(prefix, (entry + 1) * pg)] = 0
+        v[entry * pg:min(prefix, (entry + 1) * pg)] = 0
+        out = torch.full((chunk, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        hswa.prefill(layer, shape, kv.cache, to_dev(qb), to_dev(hist.k[0][prefix:]), to_dev(hist.v[0][prefix:]),
+                     i32([0, chunk]), i32([prefix]), chunk, out)
+        torch.cuda.synchronize()
+        kv.block_table[0, entry] = saved
+        assert_close(to_f64(out), OA.prefill(OA.bf16_bits_to_f64(qb), k, v, prefix, None), f"PG {pg} entry {entry}")
