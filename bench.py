@@ -58,8 +58,8 @@ MEASURED_TRAFFIC = {
                             "sha256": "33e861862964a2599c57b8f8b62732bb38b9230475ce145bad52e97f5f5aaef7",
                             "fetch_bytes": 8609499338, "write_bytes": 5574682},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
-                     "sha256": "99a626a1410b9251fbffd1b0963906a948437637c8a1a79d7386e75c4929acbe",
-                     "fetch_bytes": 452902842, "write_bytes": 141569644},
+                     "sha256": "13a03dc0de4c758324f02f37d0742aaa63e7c6b090e1c19bf4e3ce6e9534e653",
+                     "fetch_bytes": 452563859, "write_bytes": 141584516},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
                     "sha256": "1ab52ecfb56b32547d74b3a6bf166c7dc311a3e9828d48afb8205e14c9a02211",
                     "fetch_bytes": 184794072, "write_bytes": 149292872},

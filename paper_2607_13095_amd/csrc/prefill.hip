@@ -45,7 +45,9 @@ static_assert((kBufs & (kBufs - 1)) == 0, "buffer indices are taken modulo kBufs
 // a lane's share (16 probabilities) of a row sum above which the running
 // maximum is raised
 constexpr float kLaneSumLimit = 4096.f;
-constexpr int kAhead = 6;  // LDS operand reads in flight ahead of the matrix products
+// LDS operand reads in flight ahead of the matrix products (8: +0.6%, 10: +1.6%,
+// 6: +0.3% on 4 x 2048 over 8192)
+constexpr int kAhead = 4;
 // LDS holds each tile in MFMA operand order: every operand a wave reads (K: 16
 // keys x 32 dims of a QK^T step; V^T: 16 dims x 32 keys of a PV step) is a
 // contiguous 1 KiB block with lane l's 16 bytes at 16 l, so each operand read
@@ -560,32 +562,28 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
   u32x4 pf[2][kCG];
   // matrix phase: PV of tile jt-1, QK^T of tile jt, at raised issue priority
   // so that the other wave's softmax takes the issue slots the matrix
-  // products leave free
-  auto matrix_phase = [&](int jt) __attribute__((always_inline)) {
+  // products leave free. One software pipeline through both: draining it
+  // between PV and QK^T cost 1.0-1.5% (4 x 2048 over 8192 cached: 1965 -> 1947
+  // us) and 3% with one workgroup per compute unit at work (295 tokens over
+  // 22.5K: 517 -> 502 us).
+  auto matrix_phase = [&](int jt, auto first_tag) __attribute__((always_inline)) {
+    constexpr bool kFirst = decltype(first_tag)::value;
+    constexpr int kReads = kFirst ? 16 : 32;
     const int buf = jt & (kBufs - 1);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(2);
-    if (jt > 0) {
-      pv_tile((jt + kBufs - 1) & (kBufs - 1), pf);
-      // operand reads run kAhead reads ahead of the products that use them
-      __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
-#pragma unroll
-      for (int i = 0; i < 16 - kAhead; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, kCG, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, kCG * kAhead, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    if constexpr (!kFirst) pv_tile((jt + kBufs - 1) & (kBufs - 1), pf);
     qk_half(buf, 0, sc[0]);
     qk_half(buf, 1, sc[1]);
-    __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 1);
+    // operand reads run kAhead reads ahead of the products that use them, from
+    // the PV products on into the QK^T ones
+    __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
 #pragma unroll
-    for (int i = 0; i < 16 - kAhead; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
-      __builtin_amdgcn_sched_group_barrier(0x008, kCG, 1);
+    for (int i = 0; i < kReads - kAhead; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, kCG, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, kCG * kAhead, 1);
+    __builtin_amdgcn_sched_group_barrier(0x008, kCG * kAhead, 0);
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(0);
   };
@@ -615,18 +613,23 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
   };
+  constexpr std::true_type kFirstTile{};
+  constexpr std::false_type kNextTile{};
   if (!lag) {
-    for (int jt = 0; jt < ntiles; ++jt) {
-      matrix_phase(jt);
+    matrix_phase(0, kFirstTile);
+    softmax_phase(0);
+    tile_barrier();
+    for (int jt = 1; jt < ntiles; ++jt) {
+      matrix_phase(jt, kNextTile);
       softmax_phase(jt);
       tile_barrier();
     }
   } else {
-    matrix_phase(0);
+    matrix_phase(0, kFirstTile);
     tile_barrier();
     for (int jt = 1; jt < ntiles; ++jt) {
       softmax_phase(jt - 1);
-      matrix_phase(jt);
+      matrix_phase(jt, kNextTile);
       tile_barrier();
     }
     softmax_phase(ntiles - 1);
