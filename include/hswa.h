@@ -205,6 +205,24 @@ hswa_status hswa_prefill(hswa_layer layer, const hswa_shape *shape, const hswa_c
                          const int32_t *cu_seqlens, const int32_t *prefix_lens, int32_t ns,
                          int32_t total_tokens, int32_t max_chunk_len, void *out, void *stream);
 
+/* hswa_prefill with a workspace. A FULL call with few query tiles (one short
+ * chunk over a long prefix, a few ragged chunks) does not fill the device with
+ * one workgroup per tile; given a workspace, the key ranges of all tiles are
+ * cut into equal spans, one per compute unit, and the fp32 partials of a tile
+ * met by several spans are merged by the log-sum-exp identity.
+ * hswa_prefill_workspace_bytes: the bytes such a call takes (about 65 MiB,
+ * whatever its size), 0 for calls that do not gain from the split. A NULL
+ * workspace, or one given to a call that needs none, is hswa_prefill; one too
+ * small for a call that needs it is HSWA_ERR_CAPACITY. workspace: device,
+ * 16-byte aligned, free for other use once the call's work has completed. */
+size_t hswa_prefill_workspace_bytes(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache,
+                                    int32_t ns, int32_t total_tokens, int32_t max_chunk_len);
+hswa_status hswa_prefill_ws(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache,
+                            const void *q, const void *k_new, const void *v_new,
+                            const int32_t *cu_seqlens, const int32_t *prefix_lens, int32_t ns,
+                            int32_t total_tokens, int32_t max_chunk_len, void *workspace,
+                            size_t workspace_bytes, void *out, void *stream);
+
 /* Workspace bytes hswa_decode needs for a FULL layer (0 for an SWA layer is
  * enough): fp32 partial outputs and log-sum-exps of every split-KV piece
  * (at most ceil(max_context_len / hswa_decode_split_len) + 1 per output row).

@@ -186,6 +186,27 @@ hswa_status hswa_kv_append(hswa_layer layer, const hswa_shape *shape, const hswa
 hswa_status hswa_prefill(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache, const void *q,
                          const void *k_new, const void *v_new, const int32_t *cu_seqlens, const int32_t *prefix_lens,
                          int32_t ns, int32_t total_tokens, int32_t max_chunk_len, void *out, void *stream) {
+  return hswa_prefill_ws(layer, shape, cache, q, k_new, v_new, cu_seqlens, prefix_lens, ns, total_tokens,
+                         max_chunk_len, nullptr, 0, out, stream);
+}
+
+size_t hswa_prefill_workspace_bytes(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache, int32_t ns,
+                                    int32_t total_tokens, int32_t max_chunk_len) {
+  hswa::PrefillParams p{};
+  if (check_layer(layer) != HSWA_OK || check_shape(shape) != HSWA_OK) return 0;
+  if (make_pool(layer, shape, cache, p.pool) != HSWA_OK) return 0;
+  p.ns = ns;
+  p.total_tokens = total_tokens;
+  p.max_chunk_len = max_chunk_len;
+  p.hkv = shape->num_kv_heads;
+  p.group = shape->num_q_heads / p.hkv;
+  return hswa::prefill_split_fits(p) ? hswa::prefill_split_bytes() : 0;
+}
+
+hswa_status hswa_prefill_ws(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache, const void *q,
+                            const void *k_new, const void *v_new, const int32_t *cu_seqlens,
+                            const int32_t *prefix_lens, int32_t ns, int32_t total_tokens, int32_t max_chunk_len,
+                            void *workspace, size_t workspace_bytes, void *out, void *stream) {
   hswa_status st;
   if ((st = check_layer(layer)) != HSWA_OK) return st;
   if ((st = check_shape(shape)) != HSWA_OK) return st;
@@ -210,6 +231,10 @@ hswa_status hswa_prefill(hswa_layer layer, const hswa_shape *shape, const hswa_c
   p.group = p.hq / p.hkv;
   p.scale_log2 = shape->scale * 1.4426950408889634f;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (workspace && hswa::prefill_split_fits(p)) {
+    if (workspace_bytes < hswa::prefill_split_bytes()) return HSWA_ERR_CAPACITY;
+    return finish_launch(hswa::launch_prefill_split(p, workspace, s), s);
+  }
   return finish_launch(hswa::launch_prefill(p, s), s);
 }
 

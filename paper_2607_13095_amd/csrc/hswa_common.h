@@ -146,6 +146,15 @@ __device__ __forceinline__ float sum_xor32(float x) {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// The swap of lanes l and l ^ 16 for one pair of accumulator vectors (dims
+// 16 dt + 4 q .. +3 of dt = 2 pp and 2 pp + 1): 8 consecutive dims from
+// 32 pp + 16 (q % 2) + 8 (q / 2) on.
+__device__ __forceinline__ u32x4 out_row_piece(u32x2 w0, u32x2 w1) {
+  const auto s0 = __builtin_amdgcn_permlane16_swap(w0[0], w1[0], false, false);
+  const auto s1 = __builtin_amdgcn_permlane16_swap(w0[1], w1[1], false, false);
+  return u32x4{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
+}
+
 // Writes one output row from the MFMA accumulator layout: lane r + 16 q holds
 // dims 16 dt + 4 q .. +3 of row r as two bf16 pairs w[dt] (dt = 0..7). Lanes l
 // and l ^ 16 (same row) swap halves so that each holds 8 consecutive dims (dt
@@ -157,11 +166,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ void store_out_row(uint16_t *orow, const u32x2 (&w)[8], int q, bool write) {
   u32x4 v[4];
 #pragma unroll
-  for (int pp = 0; pp < 4; ++pp) {
-    const auto s0 = __builtin_amdgcn_permlane16_swap(w[2 * pp][0], w[2 * pp + 1][0], false, false);
-    const auto s1 = __builtin_amdgcn_permlane16_swap(w[2 * pp][1], w[2 * pp + 1][1], false, false);
-    v[pp] = u32x4{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
-  }
+  for (int pp = 0; pp < 4; ++pp) v[pp] = out_row_piece(w[2 * pp], w[2 * pp + 1]);
   if (!write) return;
 #pragma unroll
   for (int pp = 0; pp < 4; ++pp)

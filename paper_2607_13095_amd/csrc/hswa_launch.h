@@ -66,6 +66,14 @@ struct DecodeParams {
   int32_t split_append;
 };
 
+// Split prefill: the query tile at the start of a span, for the merge.
+struct PrefillDesc {
+  int32_t pieces;     // spans that met the tile; 0: nothing to merge here
+  int32_t tok;        // first token of the tile
+  int32_t positions;  // its positions
+  int32_t head;       // KV head
+};
+
 struct PrefillParams {
   PoolView pool;
   const uint16_t *q;      // [T][Hq][D]
@@ -76,6 +84,9 @@ struct PrefillParams {
   uint16_t *out;          // [T][Hq][D]
   int32_t ns, total_tokens, max_chunk_len, hq, hkv, group;
   float scale_log2;
+  float *ws_o;            // split: partial outputs [2 spans][256 rows][D], in accumulator order
+  float *ws_lse;          // [2 spans][256 rows]
+  PrefillDesc *ws_desc;   // [spans]
 };
 
 hipError_t launch_kv_append(const AppendParams &p, hipStream_t stream);
@@ -85,6 +96,11 @@ hipError_t launch_decode(const DecodeParams &p, hipStream_t stream);
 bool decode_append_fused(const DecodeParams &p);
 hipError_t launch_decode_append(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill(const PrefillParams &p, hipStream_t stream);
+// FULL prefill cut into equal spans of key tiles (prefill.hip): whether a call
+// gains from it, the workspace it takes (any call), the launch.
+bool prefill_split_fits(const PrefillParams &p);
+size_t prefill_split_bytes();
+hipError_t launch_prefill_split(const PrefillParams &p, void *workspace, hipStream_t stream);
 // SWA prefill whose window is at most kPrefillWindowMax keys: 128 query rows
 // per workgroup over the window's keys only (prefill_window.hip).
 constexpr int kPrefillWindowMax = 512;

@@ -28,7 +28,17 @@
 // applied only on tiles that cross the causal diagonal, the window edge or the
 // range ends. Workgroups are mapped so that each XCD works through the query
 // tiles of a few (sequence, KV head) pairs at a time and shares their K/V in L2.
+// A call with few tiles (or few in its last round) leaves compute units idle:
+// given a workspace, its key tiles are cut into equal spans instead, one per
+// workgroup, and prefill_merge_kernel combines the pieces of a tile (295 tokens
+// over 22.5K cached, 80 tiles: 498 -> 209 us). A span walks its tiles in a loop
+// around the same code; what the tile loop does not need is kept out of its
+// registers (walk state in LDS, parameters and lane addresses formed anew per
+// tile), which a plain loop spilled at +5% per key tile.
+#include <algorithm>
 #include <cfloat>
+#include <climits>
+#include <cmath>
 #include <type_traits>
 
 #include "hswa_common.h"
@@ -45,6 +55,11 @@ static_assert((kBufs & (kBufs - 1)) == 0, "buffer indices are taken modulo kBufs
 // a lane's share (16 probabilities) of a row sum above which the running
 // maximum is raised
 constexpr float kLaneSumLimit = 4096.f;
+constexpr int kSplitSpans = 256;  // spans of the split order: one workgroup per CU
+constexpr int kTileCost = 5;      // what a query tile costs besides its key tiles, in key tiles
+constexpr int kWholeSlack = 6;    // what the partials and their merge cost
+constexpr double kSplitGain = 14;  // key tiles a split has to gain (its partials, their merge, its own order)
+constexpr int kMinSpan = 8;       // least worth of a span
 // LDS operand reads in flight ahead of the matrix products (8: +0.6%, 10: +1.6%,
 // 6: +0.3% on 4 x 2048 over 8192)
 constexpr int kAhead = 4;
@@ -90,52 +105,177 @@ struct Stage {
   bool vrow;  // chunk tile: k[] holds key rows, v[] pieces follow the chunk mapping
 };
 
+// Valid tokens of sequence b (never past q / k_new / v_new / out, whatever the
+// device offsets say; none for offsets out of range).
+template <typename Params>
+__device__ __forceinline__ int chunk_len(const Params &p, int b) {
+  const int tok = p.cu_seqlens[b];
+  const int n = min(min(p.cu_seqlens[b + 1], p.total_tokens) - tok, p.max_chunk_len);
+  return tok < 0 || p.prefix_lens[b] < 0 ? 0 : n;
+}
+// Key tiles of query tile t (npos positions) of a sequence with chunk length c
+// and prefix length pre, under window w (0: none).
+__device__ __forceinline__ int key_tiles(int t, int npos, int c, int pre, int w) {
+  const int last = min(c, (t + 1) * npos) - 1;  // its last position, from pre on
+  if (t * npos > last) return 0;
+  const int lo = w > 0 ? max(0, pre + t * npos - w + 1) : 0;
+  const int cached = lo < pre ? ((pre - 1) >> 6) - (lo >> 6) + 1 : 0;
+  return cached + (last >> 6) - ((max(lo, pre) - pre) >> 6) + 1;
+}
+
+// A workgroup's place in the split order (kept in LDS: the tile loop leaves no
+// scalar registers for it).
+struct Walk {
+  int64_t one;    // worth of the query tiles of one KV head
+  int64_t per;    // worth of a span
+  int64_t u, u1;  // this span's rest [u, u1)
+  int64_t next;   // where the query tile at u ends (u1 if the span ends in it)
+  bool whole;     // every workgroup takes one whole tile, worth 1
+};
+
+typedef __attribute__((address_space(4))) const PrefillParams KernArgs;
+
 // kCG: 16-column MFMA groups per wave, 128 kCG query rows per workgroup.
 // kPage: keys of a page, 64 standing for 64 and more.
-template <int kCG, int kPage>
-__global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
+// kSplit: the work is cut into equal spans of key tiles, one per workgroup.
+template <int kCG, int kPage, bool kSplit>
+__global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
   constexpr int kRows = 8 * 16 * kCG;
   // kBufs tile buffers, each a K tile then a V^T tile (byte offsets below)
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[kBufs * kBufBytes];
+  // split: key tiles up to and including each (sequence, query tile) of one KV
+  // head, their sum and its per-wave parts, the current query tile
+  __shared__ int64_t s_cum[kSplit ? kThreads : 1], s_wave[kSplit ? kThreads / kWave : 1];
+  __shared__ Walk s_walk;
+  __shared__ int s_tile[3];
 
-  const PoolView &pv = p.pool;
+  int b, g, tq;
+  [[maybe_unused]] const int span = (int)(blockIdx.x % kXcds) * (kSplitSpans / kXcds) + (int)(blockIdx.x / kXcds);
+  if constexpr (kSplit) {
+    const PrefillParams &p = p0;
+    const int npos = kRows / p.group, ntq = (p.max_chunk_len + npos - 1) / npos;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    // Split order: the query tiles of every KV head, sequence and position, in
+    // that order, each worth its key tiles plus kTileCost, are cut into equal
+    // spans of `per`, one span per workgroup (workgroup ids go to the XCDs
+    // round-robin, so an XCD gets consecutive spans: with 8 KV heads, one
+    // head). A query tile met by several spans gets a partial result from each,
+    // merged by prefill_merge_kernel.
+    // Where no tile is longer than a span by kWholeSlack and there is a
+    // workgroup for each, every workgroup takes one whole tile instead.
+    const int idx = tid;  // (sequence, query tile) pairs: at most one per thread (checked on the host)
+    const int bb = idx / ntq;
+    int64_t n = bb < p.ns ? key_tiles(idx - bb * ntq, npos, chunk_len(p, bb), p.prefix_lens[bb], p.pool.window) : 0;
+    n += n > 0 ? kTileCost : 0;
+    const auto scan = [&](int64_t v, int64_t &sum) {  // over the workgroup; sum: of all
+#pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) {
+        const int64_t o = __shfl_up(v, off, kWave);
+        if (lane >= off) v += o;
+      }
+      __syncthreads();
+      if (lane == kWave - 1) s_wave[wave] = v;
+      __syncthreads();
+      sum = 0;
+#pragma unroll
+      for (int w = 0; w < kThreads / kWave; ++w) {
+        if (w == wave) v += sum;
+        sum += s_wave[w];
+      }
+      return v;
+    };
+    int64_t one, per = 1;
+    int64_t cum = scan(n, one);
+    const int64_t cut = max((int64_t)kMinSpan, (one * p.hkv + kSplitSpans - 1) / kSplitSpans);
+    const bool long_tile = __syncthreads_or(n > cut + kWholeSlack) != 0;
+    const bool whole = (int64_t)__syncthreads_count(n > 0) * p.hkv <= kSplitSpans && !long_tile;
+    if (whole) cum = scan(n > 0 ? 1 : 0, one);
+    else per = cut;
+    s_cum[tid] = cum;
+    const int64_t total = one * p.hkv, u = span * per;
+    if (tid == 0) s_walk = Walk{one, per, u, min(total, u + per), 0, whole};
+    if (u >= total) {
+      if (tid == 0) p.ws_desc[span].pieces = 0;
+      return;
+    }
+  } else {
+    // XCD-aware order. Workgroup ids are dealt to the XCDs round-robin; the
+    // (sequence, KV head) pairs are dealt the same way, pair x + 8k to XCD x, so
+    // every query tile of a pair runs on one XCD and shares its K/V in that L2,
+    // while pairs of unequal length (different prefixes) spread over all XCDs.
+    // Within a pair the longest query tiles (the last ones) go first.
+    const PrefillParams &p = p0;
+    const int npos = kRows / p.group, ntq = (p.max_chunk_len + npos - 1) / npos;
+    const int npairs = p.ns * p.hkv;
+    const int xcd = (int)(blockIdx.x % kXcds);
+    const int local = (int)(blockIdx.x / kXcds);
+    const int k = local / ntq;
+    tq = ntq - 1 - (local - k * ntq);
+    const int pair = xcd + kXcds * k;
+    if (pair >= npairs) return;
+    b = pair / p.hkv;
+    g = pair - b * p.hkv;
+  }
+  for (;;) {
+  int tid = threadIdx.x;
+  // opaque, so that the lane addresses below are formed anew for each query
+  // tile and not kept (and spilled) across them
+  if constexpr (kSplit) asm volatile("" : "+v"(tid));
+  // likewise the parameters: read again from the kernel's argument segment
+  const KernArgs *args = (const KernArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (kSplit) asm volatile("" : "+s"(args));
+  const auto &p = [&]() -> const auto & {
+    if constexpr (kSplit) return *args;
+    else return p0;
+  }();
+  const auto &pv = p.pool;
   const int G = p.group;
   const int npos = kRows / G;  // positions per workgroup
-
-  // XCD-aware order. Workgroup ids are dealt to the XCDs round-robin; the
-  // (sequence, KV head) pairs are dealt the same way, pair x + 8k to XCD x, so
-  // every query tile of a pair runs on one XCD and shares its K/V in that L2,
-  // while pairs of unequal length (different prefixes) spread over all XCDs.
-  // Within a pair the longest query tiles (the last ones) go first.
   const int ntq = (p.max_chunk_len + npos - 1) / npos;
-  const int npairs = p.ns * p.hkv;
-  const int xcd = (int)(blockIdx.x % kXcds);
-  const int local = (int)(blockIdx.x / kXcds);
-  const int k = local / ntq;
-  const int tq = ntq - 1 - (local - k * ntq);
-  const int pair = xcd + kXcds * k;
-  if (pair >= npairs) return;
-  const int b = pair / p.hkv, g = pair - b * p.hkv;
-
-  const int tok0 = p.cu_seqlens[b];
-  // never step outside q / k_new / v_new / out, whatever the device offsets say
-  const int C = min(min(p.cu_seqlens[b + 1], p.total_tokens) - tok0, p.max_chunk_len);
-  const int P = p.prefix_lens[b];
-  const int q0 = tq * npos;
-  if (q0 >= C || P < 0 || tok0 < 0) return;
-  const int q1 = min(C, q0 + npos) - 1;
-  const int pfirst = P + q0, plast = P + q1;
-  const int W = pv.window;
-  const int klo = W > 0 ? max(0, pfirst - W + 1) : 0;
-  const int khi = plast;
-
-  const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // uniform in a wave
   const int r = lane & 15, q = lane >> 4;
   const int hkv = p.hkv, hq = p.hq;
   const int shift = pv.pg_shift, pg = 1 << shift;
   const float c2 = p.scale_log2;
+
+  int j0 = 0, j1 = 0;  // split: key tiles [j0, j1) of the query tile
+  if constexpr (kSplit) {
+    // the query tile that holds unit u
+    __syncthreads();
+    const int64_t gl = s_walk.u / s_walk.one;
+    const int64_t rem = s_walk.u - gl * s_walk.one;
+    const int64_t lo = tid > 0 ? s_cum[tid - 1] : 0, hi = s_cum[tid];
+    if (lo <= rem && rem < hi) {
+      s_tile[0] = tid;
+      const int64_t left = min(hi - rem, s_walk.u1 - s_walk.u);
+      s_tile[1] = (int)max((int64_t)0, rem - lo - kTileCost);
+      s_tile[2] = s_walk.whole ? INT_MAX : (int)(rem + left - lo - kTileCost);
+      s_walk.next = s_walk.u + left;
+    }
+    __syncthreads();
+    g = __builtin_amdgcn_readfirstlane((int)gl);
+    const int tile = __builtin_amdgcn_readfirstlane(s_tile[0]);
+    b = tile / ntq;
+    tq = tile - b * ntq;
+    j0 = __builtin_amdgcn_readfirstlane(s_tile[1]);
+    j1 = __builtin_amdgcn_readfirstlane(s_tile[2]);
+    if (j1 <= 0) {  // the span ends before the tile's first key tile
+      if (tid == 0 && s_walk.u == span * s_walk.per) p.ws_desc[span].pieces = 0;
+      return;
+    }
+  }
+
+  const int tok0 = p.cu_seqlens[b];
+  const int C = chunk_len(p, b);
+  const int P = p.prefix_lens[b];
+  const int q0 = tq * npos;
+  if (!kSplit && q0 >= C) return;
+  const int q1 = min(C, q0 + npos) - 1;
+  const int pfirst = P + q0, plast = P + q1;
+  const int W = pv.window;
+  const int klo = W > 0 ? max(0, pfirst - W + 1) : 0;
+  const int khi = plast;
 
   // Q^T operands and the position of each of this lane's columns.
   u32x4 qf[kCG][4];
@@ -162,10 +302,12 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
   // Cut at P: tiles of cached keys, aligned to 64 absolute positions (so that a
   // tile is whole pool blocks), then tiles of the chunk's own keys, aligned to
   // P. No tile holds both kinds; a tile at an end of its range is partly masked.
-  const int kt0 = klo & ~(kKT - 1);
-  const int ncached = klo < P ? ((P - 1) >> 6) - (klo >> 6) + 1 : 0;
   const int nlo = max(klo, P);  // first new key in range
-  const int ntiles = ncached + ((khi - P) >> 6) - ((nlo - P) >> 6) + 1;
+  const int nall = key_tiles(tq, npos, C, P, W);
+  // this workgroup's tiles, numbered from j0 on (ncached <= 0: no cached one)
+  const int ntiles = kSplit ? min(j1, nall) - j0 : nall;
+  const int ncached = (klo < P ? ((P - 1) >> 6) - (klo >> 6) + 1 : 0) - j0;
+  const int kt0 = (klo & ~(kKT - 1)) + kKT * j0;
   const int ktn = P + ((nlo - P) & ~(kKT - 1)) - kKT * ncached;  // tile j >= ncached starts at ktn + 64 j
   auto tile_key = [&](int j) { return kKT * j + (j < ncached ? kt0 : ktn); };
 
@@ -547,14 +689,16 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     }
   };
 
+  // the first three tiles' loads go out together (no accumulator is live yet)
   Stage st;
-  fetch(0, st);
-  store_tile(0, st);
-  if (ntiles > 1) {
-    fetch(1, st);
-    store_tile(1, st);
+  {
+    Stage s0, s1;
+    fetch(0, s0);
+    fetch(min(1, ntiles - 1), s1);
+    fetch(min(2, ntiles - 1), st);
+    store_tile(0, s0);
+    if (ntiles > 1) store_tile(1, s1);
   }
-  if (ntiles > 2) fetch(2, st);
   __syncthreads();
   const bool lag = wave >= kThreads / kWave / 2;  // group B
 
@@ -637,6 +781,47 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
   pv_tile((ntiles + kBufs - 1) & (kBufs - 1), pf);
 
   // ---- normalise and write ----
+  bool last = !kSplit;
+  if constexpr (kSplit) {
+    const int64_t u = s_walk.u, per = s_walk.per;
+    const bool whole = ntiles == nall;
+    if (tid == 0 && u == span * per) {
+      // the span's first query tile, for the merge: it takes up a tile at the
+      // second of its spans
+      const int64_t k0 = u - j0, first = k0 / per;  // k0: the place of the tile's first key tile, if j0 > 0
+      PrefillDesc d;
+      d.pieces = j0 > 0 && first + 1 == span ? (int)((k0 + nall - 1) / per - first) + 1 : 0;
+      d.tok = tok0 + q0;
+      d.positions = q1 - q0 + 1;
+      d.head = g;
+      p.ws_desc[span] = d;
+    }
+    if (!whole) {
+      // a piece of the query tile: slot 2 span + 1 for its first key tiles,
+      // slot 2 span for later ones (the span's last and first piece);
+      // accumulators in register order (1 KiB runs)
+      const int64_t base = ((int64_t)(2 * span + (j0 == 0 ? 1 : 0)) * 8 + wave) * kCG;
+#pragma unroll
+      for (int cg = 0; cg < kCG; ++cg) {
+        const float l = sum_xor32(sum_xor16(lsum[cg]));
+        // a row that sees no key of this piece: o = 0, log-sum-exp -inf
+        const float inv = l != 0.f ? 1.f / l : 0.f;
+        f32x4 *dst = reinterpret_cast<f32x4 *>(p.ws_o) + (base + cg) * 8 * kWave + lane;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) dst[dt * kWave] = acc[cg][dt] * inv;
+        if (q == 0) p.ws_lse[(base + cg) * 16 + r] = m[cg] + __log2f(l);
+      }
+    }
+    const int64_t unext = s_walk.next;
+    const bool done = unext >= s_walk.u1;
+    __syncthreads();  // every wave has read s_walk and the tile buffers
+    if (tid == 0) s_walk.u = unext;
+    if (!whole) {
+      if (done) return;
+      continue;
+    }
+    if (done) last = true;
+  }
 #pragma unroll
   for (int cg = 0; cg < kCG; ++cg) {
     const float l = sum_xor32(sum_xor16(lsum[cg]));
@@ -652,28 +837,113 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
     }
     store_out_row(orow, w, q, cval[cg]);
   }
+  if (last) break;
+  }
+}
+
+// Log-sum-exp merge of the query tiles that several spans met. One workgroup
+// per 16 rows of the tile that the first boundary of a span cuts; wave pp
+// merges dims 32 pp .. +31 (the accumulator vectors 2 pp and 2 pp + 1).
+template <int kCG>
+__global__ __launch_bounds__(4 * kWave) void prefill_merge_kernel(PrefillParams p) {
+  constexpr int kParts = 8 * kCG;  // 16-row groups of a tile
+  const int span = 1 + (int)(blockIdx.x / kParts), part = (int)(blockIdx.x % kParts);
+  const PrefillDesc d = p.ws_desc[span];
+  if (d.pieces == 0) return;
+  const int lane = threadIdx.x & (kWave - 1), pp = threadIdx.x / kWave;
+  const int r = lane & 15, q = lane >> 4;
+  // piece 0 lies in slot 2 (span - 1) + 1, piece i in slot 2 (span - 1 + i)
+  auto group_of = [&](int i) { return (int64_t)(2 * (span - 1 + i) + (i == 0 ? 1 : 0)) * kParts + part; };
+  float mx = -INFINITY;
+#pragma unroll 4
+  for (int i = 0; i < d.pieces; ++i) mx = fmaxf(mx, p.ws_lse[group_of(i) * 16 + r]);
+  const f32x4 *src = reinterpret_cast<const f32x4 *>(p.ws_o) + 2 * pp * kWave + lane;
+  float wsum = 0.f;
+  f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0;
+#pragma unroll 4
+  for (int i = 0; i < d.pieces; ++i) {
+    const int64_t gi = group_of(i);
+    const float w = fast_exp2(p.ws_lse[gi * 16 + r] - mx);
+    wsum += w;
+    o0 += w * src[gi * 8 * kWave];
+    o1 += w * src[gi * 8 * kWave + kWave];
+  }
+  const float inv = 1.f / wsum;
+  const u32x2 w0 = {pack_bf16x2(o0[0] * inv, o0[1] * inv), pack_bf16x2(o0[2] * inv, o0[3] * inv)};
+  const u32x2 w1 = {pack_bf16x2(o1[0] * inv, o1[1] * inv), pack_bf16x2(o1[2] * inv, o1[3] * inv)};
+  const u32x4 v = out_row_piece(w0, w1);
+  const int row = part * 16 + r;
+  const int po = row / p.group, head = row - po * p.group;
+  if (po >= d.positions) return;
+  uint16_t *orow = p.out + ((int64_t)(d.tok + po) * p.hq + (int64_t)d.head * p.group + head) * kHeadDim;
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(orow + 32 * pp + 16 * (q & 1) + 8 * (q >> 1)));
 }
 
 }  // namespace
 
-template <int kCG>
-hipError_t launch_prefill_rows(const PrefillParams &p, hipStream_t stream) {
-  const int npos = 128 * kCG / p.group;
-  const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
-  const int64_t pairs_per_xcd = ((int64_t)p.ns * p.hkv + kXcds - 1) / kXcds;
-  const dim3 grid((unsigned)(pairs_per_xcd * ntq * kXcds)), block(kThreads);
+constexpr int kRowGroups = 2;  // 16-column MFMA groups per wave: 256 query rows per workgroup
+
+template <bool kSplit>
+hipError_t launch_prefill_rows(const PrefillParams &p, dim3 grid, hipStream_t stream) {
+  const dim3 block(kThreads);
   switch (p.pool.pg_shift) {
-    case 4: return launch_kernel(prefill_kernel<kCG, 16>, grid, block, stream, p);
-    case 5: return launch_kernel(prefill_kernel<kCG, 32>, grid, block, stream, p);
-    default: return launch_kernel(prefill_kernel<kCG, 64>, grid, block, stream, p);
+    case 4: return launch_kernel(prefill_kernel<kRowGroups, 16, kSplit>, grid, block, stream, p);
+    case 5: return launch_kernel(prefill_kernel<kRowGroups, 32, kSplit>, grid, block, stream, p);
+    default: return launch_kernel(prefill_kernel<kRowGroups, 64, kSplit>, grid, block, stream, p);
   }
+}
+
+// Whether a FULL call is cut into spans of key tiles. The host knows the chunk
+// lengths only by their largest and their sum, and the prefix lengths only as
+// what the block table can hold; in key tiles it takes the unsplit call as the
+// largest of its longest tile, its rounds of the shortest tiles and its average
+// load on the fullest XCD, and the split one as the average over all compute
+// units. The line of kSplitGain is where both measured the same: with 64 / 8
+// heads, 64 tokens over 1000 cached (gain 14) 32 us unsplit and 29 split, 8 x
+// 64 over 1000 (11) 37 and 41, 1500 over none (3) 48 and 66, 4 x 2048 over
+// 8192 (0) 1915 and 2150, 4 ragged chunks at PG 16 (60) 138 and 115, 295 over
+// 22.5K (246) 498 and 209, 32 over 32768 (480) 698 and 54.
+bool prefill_split_fits(const PrefillParams &p) {
+  if (p.pool.window > 0 || p.ns <= 0 || p.max_chunk_len <= 0 || p.total_tokens <= 0) return false;
+  const int npos = 128 * kRowGroups / p.group;
+  const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
+  if (ntq * p.ns > kThreads) return false;  // one (sequence, query tile) pair per thread
+  const double keys = (double)(((int64_t)p.pool.stride << p.pool.pg_shift) / kKT);
+  const double chunk = std::min<double>(keys, (double)p.max_chunk_len / kKT);
+  const double longest = keys + kTileCost, average = longest - chunk / 2, shortest = longest - chunk;
+  const double tiles = (double)(std::min<int64_t>(ntq * p.ns, p.total_tokens / npos + p.ns) * p.hkv) / kSplitSpans;
+  const int64_t pairs = (int64_t)p.ns * p.hkv;
+  const double load = (double)((pairs + kXcds - 1) / kXcds * ntq) / (kSplitSpans / kXcds);  // tiles per CU
+  const double unsplit = std::max({longest, std::ceil(load) * shortest, load * average});
+  return unsplit - std::max((double)kMinSpan, tiles * average) >= kSplitGain;
+}
+
+// fp32 partials, their log-sum-exps and a descriptor per span.
+constexpr size_t kSplitOBytes = (size_t)2 * kSplitSpans * 128 * kRowGroups * kHeadDim * 4;
+constexpr size_t kSplitLseBytes = (size_t)2 * kSplitSpans * 128 * kRowGroups * 4;
+
+size_t prefill_split_bytes() { return kSplitOBytes + kSplitLseBytes + kSplitSpans * sizeof(PrefillDesc); }
+
+hipError_t launch_prefill_split(const PrefillParams &p0, void *workspace, hipStream_t stream) {
+  PrefillParams p = p0;
+  char *ws = static_cast<char *>(workspace);
+  p.ws_o = reinterpret_cast<float *>(ws);
+  p.ws_lse = reinterpret_cast<float *>(ws + kSplitOBytes);
+  p.ws_desc = reinterpret_cast<PrefillDesc *>(ws + kSplitOBytes + kSplitLseBytes);
+  const hipError_t e = launch_prefill_rows<true>(p, dim3(kSplitSpans), stream);
+  if (e != hipSuccess) return e;
+  return launch_kernel(prefill_merge_kernel<kRowGroups>, dim3((kSplitSpans - 1) * 8 * kRowGroups), dim3(4 * kWave),
+                       stream, p);
 }
 
 hipError_t launch_prefill(const PrefillParams &p, hipStream_t stream) {
   if (p.ns <= 0 || p.max_chunk_len <= 0 || p.total_tokens <= 0) return hipSuccess;
   if (p.pool.window > 0 && prefill_run_fits(p)) return launch_prefill_run(p, stream);
   if (p.pool.window > 0 && p.pool.window <= kPrefillWindowMax) return launch_prefill_window(p, stream);
-  return launch_prefill_rows<2>(p, stream);
+  const int npos = 128 * kRowGroups / p.group;
+  const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
+  const int64_t pairs_per_xcd = ((int64_t)p.ns * p.hkv + kXcds - 1) / kXcds;
+  return launch_prefill_rows<false>(p, dim3((unsigned)(pairs_per_xcd * ntq * kXcds)), stream);
 }
 
 }  // namespace hswa

@@ -33,7 +33,7 @@ EXPORTS = ["hswa_ring_pages", "hswa_page_bytes", "hswa_build_block_table", "hswa
            "hswa_prefix_tree_create", "hswa_prefix_tree_destroy", "hswa_prefix_tree_insert",
            "hswa_prefix_tree_match", "hswa_prefix_tree_release_swa", "hswa_prefix_tree_evict",
            "hswa_prefix_tree_stats", "hswa_decode_multi_workspace_bytes", "hswa_decode_multi",
-           "hswa_decode_noalloc", "hswa_decode_append"]
+           "hswa_decode_noalloc", "hswa_decode_append", "hswa_prefill_workspace_bytes", "hswa_prefill_ws"]
 
 # bytes of the library's fixed device array behind hswa_decode_noalloc
 NOALLOC_SCRATCH_BYTES = 128 << 20
@@ -89,6 +89,8 @@ def load():
         "hswa_build_block_table": (ctypes.c_int, [LP, I32, I32, P, P, I64, P, I32]),
         "hswa_kv_append": (ctypes.c_int, [LP, SP, CP, P, P, P, P, I32, I32, P, P]),
         "hswa_prefill": (ctypes.c_int, [LP, SP, CP, P, P, P, P, P, I32, I32, I32, P, P]),
+        "hswa_prefill_workspace_bytes": (SZ, [LP, SP, CP, I32, I32, I32]),
+        "hswa_prefill_ws": (ctypes.c_int, [LP, SP, CP, P, P, P, P, P, I32, I32, I32, P, SZ, P, P]),
         "hswa_decode_workspace_bytes": (SZ, [SP, I32, I32]),
         "hswa_decode_split_len": (I32, [SP, I32, I32]),
         "hswa_decode": (ctypes.c_int, [LP, SP, CP, P, P, I32, I32, P, SZ, P, P]),
@@ -343,9 +345,38 @@ def kv_append(layer: Layer, shape: Shape, cache: Cache, k_new, v_new, cu_seqlens
     _check(st, "hswa_kv_append")
 
 
+def _prefill_scratch(nbytes: int, stream):
+    """Scratch for one call from torch's caching allocator, in the order of the
+    stream the call runs on, or None (the call then runs unsplit): on a raw
+    stream handle the allocator does not know, when the device is out of memory,
+    and under a stream capture that torch did not begin. (A graph captured by
+    torch owns the memory it allocates; in another capture the memory would be
+    handed out again while the graph still replays into it.)"""
+    torch = _torch()
+    if isinstance(stream, int):
+        return None
+    with torch.cuda.stream(stream):
+        try:
+            t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        except torch.cuda.OutOfMemoryError:
+            return None
+        if torch.cuda.is_current_stream_capturing() and not _in_private_pool(t):
+            return None
+        return t
+
+
+def _in_private_pool(t) -> bool:
+    """Whether the tensor's memory belongs to a graph's (or another private) pool."""
+    a = t.data_ptr()
+    return any(s["address"] <= a < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
+               for s in _torch().cuda.memory_snapshot())
+
+
 def prefill(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, cu_seqlens, prefix_lens,
             max_chunk_len: int, out, stream=None):
-    """Chunked prefill; q, out [T, Hq, D], k_new / v_new [T, Hkv, D]; see hswa_prefill."""
+    """Chunked prefill; q, out [T, Hq, D], k_new / v_new [T, Hkv, D]; see
+    hswa_prefill and, for FULL calls with few query tiles, hswa_prefill_ws
+    (their scratch is held for the length of the call only)."""
     ns = int(cu_seqlens.numel()) - 1
     t = int(q.shape[0])
     qrow, krow = shape.num_q_heads * shape.head_dim, shape.num_kv_heads * shape.head_dim
@@ -355,8 +386,13 @@ def prefill(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, cu_seqlen
     o = _ptr(out, "out", _bf16(), t * qrow)
     _check_cache(shape, cache, ns)
     sh, ca = shape.c(), cache.c()
-    st = load().hswa_prefill(layer.c(), ctypes.byref(sh), ctypes.byref(ca), *args, ns, t, int(max_chunk_len), o,
-                             _stream(stream))
+    lib, lc, sp, cp, mc = load(), layer.c(), ctypes.byref(sh), ctypes.byref(ca), int(max_chunk_len)
+    need = lib.hswa_prefill_workspace_bytes(lc, sp, cp, ns, t, mc)
+    ws = _prefill_scratch(need, stream) if need else None
+    if ws is None:
+        st = lib.hswa_prefill(lc, sp, cp, *args, ns, t, mc, o, _stream(stream))
+    else:
+        st = lib.hswa_prefill_ws(lc, sp, cp, *args, ns, t, mc, ws.data_ptr(), need, o, _stream(stream))
     _check(st, "hswa_prefill")
 
 

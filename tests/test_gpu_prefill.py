@@ -179,3 +179,53 @@ def test_prefill_invalid_page_reads_as_zero(gpu_lib, pg):
         torch.cuda.synchronize()
         kv.block_table[0, entry] = saved
         assert_close(to_f64(out), OA.prefill(OA.bf16_bits_to_f64(qb), k, v, prefix, None), f"PG {pg} entry {entry}")
+
+
+@pytest.mark.parametrize("pg,hq,hkv,prefixes,chunks", [
+    (64, 16, 2, [5000], [33]),                        # one tile row, cut into many pieces
+    (16, 8, 1, [3001, 0, 700], [70, 1, 129]),         # pieces inside the cached and the new keys
+    (32, 8, 4, [1100, 0, 64, 2047], [90, 0, 300, 5]),  # an empty chunk; 128 positions a tile
+    (128, 64, 1, [1024], [9]),                        # four positions a tile, no key past the first page run
+    (64, 32, 8, [0], [1500]),                         # no cached key: causal tiles of unequal length
+])
+def test_prefill_split(gpu_lib, pg, hq, hkv, prefixes, chunks):
+    """Calls cut into spans of key tiles, against the oracle and the unsplit call
+    (both round the same fp32 sums, taken in another order, to bf16)."""
+    print(f"[prefill-split] pg={pg} {hq}/{hkv} {prefixes} {chunks}", flush=True)
+    gpu, ref, (layer, shape, kv, hist, kn, vn) = run_prefill("full", 0, pg, hq, hkv, prefixes, chunks,
+                                                             (205, pg, hq, hkv))
+    ns, t, mc = len(chunks), sum(chunks), max(chunks)
+    lib, sh, ca = hswa.load(), shape.c(), kv.cache.c()
+    need = lib.hswa_prefill_workspace_bytes(layer.c(), sh, ca, ns, t, mc)
+    assert need > 0
+    assert_close(gpu, ref, f"split prefill {prefixes} {chunks}")
+    q = to_dev(synth.normal_bf16((t, hq, 128), 205, pg, hq, hkv, synth.TAG_Q))
+    k, v, cu, pre = to_dev(kn), to_dev(vn), i32(synth.cu_seqlens(chunks)), i32(prefixes)
+    out = torch.full((t, hq, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ptr = [x.data_ptr() for x in (q, k, v, cu, pre)]
+    stream = torch.cuda.current_stream().cuda_stream
+    assert lib.hswa_prefill(layer.c(), sh, ca, *ptr, ns, t, mc, out.data_ptr(), stream) == 0
+    torch.cuda.synchronize()
+    assert_close(gpu, to_f64(out), f"split against unsplit {prefixes} {chunks}")
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    assert lib.hswa_prefill_ws(layer.c(), sh, ca, *ptr, ns, t, mc, ws.data_ptr(), 256, out.data_ptr(), stream) == -3
+
+
+@pytest.mark.parametrize("prefix,chunk", [(130, 70), (0, 40), (1500, 40)])
+def test_prefill_split_table_larger_than_context(gpu_lib, prefix, chunk):
+    """The split is chosen by what the block table can hold; contexts far shorter
+    than that run as whole tiles (the first two) or in short spans."""
+    print(f"[prefill-split] table for 9000, {chunk} over {prefix}", flush=True)
+    shape = hswa.Shape(32, 4, 128, 64)
+    layer, kv = make_layer("full", 0, shape, [9000], (206, prefix))
+    hist = SeqHistory([prefix + chunk], 4, 128, 206, prefix)
+    append_history(layer, shape, kv, hist, [0], [prefix])
+    assert hswa.load().hswa_prefill_workspace_bytes(layer.c(), shape.c(), kv.cache.c(), 1, chunk, chunk) > 0
+    qb = synth.normal_bf16((chunk, 32, 128), 206, prefix, synth.TAG_Q)
+    out = torch.full((chunk, 32, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    hswa.prefill(layer, shape, kv.cache, to_dev(qb), to_dev(hist.k[0][prefix:]), to_dev(hist.v[0][prefix:]),
+                 i32([0, chunk]), i32([prefix]), chunk, out)
+    torch.cuda.synchronize()
+    ref = OA.prefill(OA.bf16_bits_to_f64(qb), OA.bf16_bits_to_f64(hist.k[0]), OA.bf16_bits_to_f64(hist.v[0]), prefix,
+                     None)
+    assert_close(to_f64(out), ref, f"{chunk} over {prefix}")
