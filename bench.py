@@ -55,14 +55,14 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 # measured again.
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
-                            "sha256": "33e861862964a2599c57b8f8b62732bb38b9230475ce145bad52e97f5f5aaef7",
-                            "fetch_bytes": 8609499338, "write_bytes": 5574682},
+                            "sha256": "fe66ea7ff4d95408d8647f1bd5ed3f3e5a317c8cdabfaa9b2cb3d5398836b9d8",
+                            "fetch_bytes": 8609332060, "write_bytes": 5574380},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
-                     "sha256": "13a03dc0de4c758324f02f37d0742aaa63e7c6b090e1c19bf4e3ce6e9534e653",
-                     "fetch_bytes": 452563859, "write_bytes": 141584516},
+                     "sha256": "03bd7ef7488d051e66129efe8e554844883ae506ab9d3e0fff885778e8d7771d",
+                     "fetch_bytes": 453050655, "write_bytes": 141396675},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
-                    "sha256": "1ab52ecfb56b32547d74b3a6bf166c7dc311a3e9828d48afb8205e14c9a02211",
-                    "fetch_bytes": 184794072, "write_bytes": 149292872},
+                    "sha256": "77f83496157450bb04bc33bb220be9e72192ff05e63f4b08f071d56c493dffb5",
+                    "fetch_bytes": 184782520, "write_bytes": 149726034},
 }
 
 
