@@ -55,14 +55,14 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 # measured again.
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
-                            "sha256": "fe66ea7ff4d95408d8647f1bd5ed3f3e5a317c8cdabfaa9b2cb3d5398836b9d8",
-                            "fetch_bytes": 8609332060, "write_bytes": 5574380},
+                            "sha256": "4efb2e0317ba54068bb87f5b63665fe62b334af57391b9b2f4e4c24e94bc399f",
+                            "fetch_bytes": 8609292759, "write_bytes": 5573663},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
-                     "sha256": "03bd7ef7488d051e66129efe8e554844883ae506ab9d3e0fff885778e8d7771d",
-                     "fetch_bytes": 453050655, "write_bytes": 141396675},
+                     "sha256": "ba494e313af1e8dabd10fb160a420f29f4bc5c65788a36993632c3da1378c557",
+                     "fetch_bytes": 453002322, "write_bytes": 141376768},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
-                    "sha256": "77f83496157450bb04bc33bb220be9e72192ff05e63f4b08f071d56c493dffb5",
-                    "fetch_bytes": 184782520, "write_bytes": 149726034},
+                    "sha256": "6efdd4bfa3ccfc2d92754704e8dc6c9f8a0041c8d251147d861c926c6a485d88",
+                    "fetch_bytes": 184782131, "write_bytes": 149697731},
 }
 
 

@@ -30,9 +30,9 @@
 // gets fp32 (o, log2 sum-exp) partials that a second kernel merges; a segment
 // inside one span, and a whole-range item, is written as bf16 directly.
 // In a decode step with its append ("KVCache Dual-Pool Design": the step's
-// token goes to its slot), the split spans of one-page chunks also store the
-// token: the wave holding a segment's last chunk takes the token's key from
-// the input rows and writes them to the slot.
+// token goes to its slot), the split spans also store the token: the wave
+// holding a segment's last chunk takes the token's key from the input rows and
+// writes them to the slot.
 #include <atomic>
 #include <cfloat>
 
@@ -119,6 +119,11 @@ struct Chunk {
   bool vok;
 };
 
+// Pages of one chunk: a, and for PG = 16 b (the chunk's second 16 keys).
+struct ChunkPages {
+  int a, b;
+};
+
 // A workgroup holds four waves. Split (FULL): each wave walks a span of its
 // own. Whole ranges (an SWA window, or a FULL context of one pass: only
 // sequences x head groups items, each a short chain of dependent chunk
@@ -133,10 +138,11 @@ constexpr int kCoop = kSplit ? 1 : kWaves;  // waves that share one item
 // (query, head) columns of a KV head) one wave scores both against the same
 // K/V loads, which halves the KV bytes read. Whole-range items: with one group
 // a wave has at most 168 VGPRs, so that three waves share a SIMD (two with two
-// groups). Split spans with one page per chunk (PG >= 32): one wave per SIMD,
-// which leaves room for two chunks of operands in flight.
+// groups). Split spans: one wave per SIMD,
+// which leaves room for two chunks of operands in flight. kOnePage: a chunk's
+// keys lie in one page (PG >= 32), else in two (PG = 16).
 template <bool kSplit, bool kOnePage, int kCGd>
-__global__ __launch_bounds__(kWave * kWaves) __attribute__((amdgpu_waves_per_eu(kSplit && kOnePage ? 1 : (kCGd == 1 ? 3 : 2))))
+__global__ __launch_bounds__(kWave * kWaves) __attribute__((amdgpu_waves_per_eu(kSplit ? 1 : (kCGd == 1 ? 3 : 2))))
 void decode_kernel(DecodeParams p) {
   const PoolView &pv = p.pool;
   const int lane = threadIdx.x & (kWave - 1);
@@ -149,16 +155,17 @@ void decode_kernel(DecodeParams p) {
   const int ncols = p.nq * p.group;  // (query, head) pairs of one KV head
   const int hchunks = (ncols + kCols * kCGd - 1) / (kCols * kCGd);  // column items per KV head
 
-  // Loop-invariant byte offsets of this lane's operands inside one 32-key K
-  // block (used when a 32-key chunk never straddles two pages, i.e. PG >= 32):
-  // slab t of half a (keys 8i + j, j < 4: MFMA rows 4i + j) is the A operand
-  // of step t in lane order, a contiguous 1 KiB; half b (keys 8i + 4 + j) 4 KiB on.
-  const uint32_t koff_a = lane * 16;
-  const uint32_t koff_b = koff_a + 4096;
-  // V^T of a 32-key chunk is one [D][32] block when PG >= 32: lane reads dims
-  // 16 dt + r, keys 8 q .. 8 q + 7 of it.
-  const uint32_t voff = (r * 32 + 8 * q) * 2;
-  const uint32_t vstep = 16 * 32 * 2;  // 16 dims of a V block
+  // Loop-invariant byte offsets of this lane's operands inside a key block.
+  // PG >= 32: slab t of half a (keys 8i + j, j < 4: MFMA rows 4i + j) of a
+  // 32-key K block is the A operand of step t in lane order, a contiguous
+  // 1 KiB; half b (keys 8i + 4 + j) 4 KiB on. The V^T of the chunk is one
+  // [D][32] block: lane reads dims 16 dt + r, keys 8 q .. 8 q + 7 of it.
+  // PG = 16: the same pieces of the two 16-key blocks, 8 rows a slab.
+  const uint32_t koff_a = kOnePage ? lane * 16 : (q * 8 + (r & 7)) * 16;
+  constexpr uint32_t kslab = kOnePage ? 1024 : 512;
+  const uint32_t koff_b = koff_a + 4 * kslab;
+  const uint32_t voff = kOnePage ? (r * 32 + 8 * q) * 2 : r * 32 + (q & 1) * 16;
+  constexpr uint32_t vstep = kOnePage ? 16 * 32 * 2 : 16 * 16 * 2;  // 16 dims of a V block
 
   // Which work this wave runs. Whole ranges: one item per workgroup, in
   // (sequence, head group) order. Split (FULL layers): the 32-key chunks of
@@ -281,11 +288,10 @@ void decode_kernel(DecodeParams p) {
       const int cfirst = kb & ~(kChunk - 1);
       const int nchunks = ((ke - cfirst) >> 5) + 1;
       const int c0 = kSplit ? 0 : wid;  // first chunk of this wave
-      const int klo8 = kb & ~7, khi8 = ke & ~7;
       const int last_lp = ke >> shift;
 
       LaneTable tab;
-      load_lane_table(tab, pv, b, kb >> shift, last_lp, lane);
+      load_lane_table(tab, pv, b, cfirst >> shift, last_lp, lane);
 
       // Running column maxima in exp2 units (score * scale * log2 e): a finite
       // start whatever the scale, raised lazily (see scores).
@@ -299,58 +305,36 @@ void decode_kernel(DecodeParams p) {
         for (int i = 0; i < 8; ++i) acc[cg][i] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
 
-      auto issue_k = [&](int c, int page, Chunk &ch) {
+      // Pages of a chunk: one (PG >= 32), or two of 16 keys, of which a lane
+      // reads the one that holds its K rows (r >> 3) and its V keys (q >> 1).
+      auto page_base = [&](int cbase, int page) {  // byte offset of the chunk's first block, or of the page
+        const int64_t ph = ((int64_t)max(page, 0) * hkv + g) << (shift + kHeadDimShift + 1);
+        return kOnePage ? ph + ((int64_t)((cbase & (pg - 1)) >> 5) << (5 + kHeadDimShift + 1)) : ph;
+      };
+      auto issue_k = [&](int c, ChunkPages pages, Chunk &ch) {
         const int cbase = cfirst + c * kChunk;
-        const int64_t pg64 = max(page, 0);
-        const char *kbase = reinterpret_cast<const char *>(pv.k_pool) +
-                            ((((pg64 * hkv + g) << shift) + (cbase & (pg - 1))) * kHeadDim) * 2;
+        int64_t o = page_base(cbase, pages.a);
+        if constexpr (!kOnePage) o = r & 8 ? page_base(cbase, pages.b) : o;
+        const char *kbase = reinterpret_cast<const char *>(pv.k_pool) + o;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          ch.ka[t] = ldnt128(kbase + koff_a + 1024 * t);
-          ch.kb[t] = ldnt128(kbase + koff_b + 1024 * t);
+          ch.ka[t] = ldnt128(kbase + koff_a + kslab * t);
+          ch.kb[t] = ldnt128(kbase + koff_b + kslab * t);
         }
       };
-      auto issue_v = [&](int c, int page, Chunk &ch) {
+      auto issue_v = [&](int c, ChunkPages pages, Chunk &ch) {
         const int cbase = cfirst + c * kChunk;
-        const int64_t pg64 = max(page, 0);
-        // PG >= 32 here, so VB = 32: the chunk is block (cbase mod PG) / 32 of the page-head
-        const char *vbase = reinterpret_cast<const char *>(pv.v_pool) +
-                            ((((pg64 * hkv + g) << shift) << kHeadDimShift) +
-                             ((int64_t)((cbase & (pg - 1)) >> 5) << (5 + kHeadDimShift))) * 2;
+        int64_t o = page_base(cbase, pages.a);
+        int page = pages.a;
+        if constexpr (!kOnePage) {
+          o = q & 2 ? page_base(cbase, pages.b) : o;
+          page = q & 2 ? pages.b : page;
+        }
+        const char *vbase = reinterpret_cast<const char *>(pv.v_pool) + o;
         ch.kv0 = cbase + 8 * q;
         ch.vok = page >= 0;
 #pragma unroll
         for (int dt = 0; dt < 8; ++dt) ch.v[dt] = ldnt128(vbase + voff + dt * vstep);
-      };
-      // General path (PG = 16: a chunk spans two pages): per-lane page choice.
-      auto issue = [&](int c, Chunk &ch) {
-        const int cbase = cfirst + c * kChunk;
-        const int lpc = max(cbase, kb) >> shift;  // first page of the chunk's valid keys
-        if ((min(cbase + kChunk - 1, ke) >> shift) - tab.lp0 >= kWave) load_lane_table(tab, pv, b, lpc, last_lp, lane);
-        const int rel = lpc - tab.lp0;
-        const int pg0 = __builtin_amdgcn_readlane(tab.page, rel);
-        const int pg1 = __builtin_amdgcn_readlane(tab.page, min(rel + 1, kWave - 1));
-        const int ka = min(max(cbase + 8 * (r >> 2) + (r & 3), kb), ke);
-        const int kb2 = min(max(cbase + 8 * (r >> 2) + 4 + (r & 3), kb), ke);
-        const int kvg = min(max(cbase + 8 * q, klo8), khi8);
-        const int pa = (ka >> shift) == lpc ? pg0 : pg1;
-        const int pb = (kb2 >> shift) == lpc ? pg0 : pg1;
-        const int pvv = (kvg >> shift) == lpc ? pg0 : pg1;
-        ch.kv0 = cbase + 8 * q;
-        ch.vok = pvv >= 0;
-        const int64_t pa64 = max(pa, 0), pb64 = max(pb, 0), pv64 = max(pvv, 0);
-        // dims 32 t + 8 q .. +7 of a key: slab t of its half, 16 * B elements apart
-        const int64_t kstep = (int64_t)16 << pv.vb_shift;
-        const uint16_t *krow_a = pv.k_pool + k_offset(pv, pa64, hkv, g, ka & (pg - 1), 8 * q);
-        const uint16_t *krow_b = pv.k_pool + k_offset(pv, pb64, hkv, g, kb2 & (pg - 1), 8 * q);
-        const uint16_t *vcol = pv.v_pool + v_offset(pv, pv64, hkv, g, kvg & (pg - 1), r);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          ch.ka[t] = ldnt128(krow_a + kstep * t);
-          ch.kb[t] = ldnt128(krow_b + kstep * t);
-        }
-#pragma unroll
-        for (int dt = 0; dt < 8; ++dt) ch.v[dt] = ldnt128(vcol + ((int64_t)(16 * dt) << pv.vb_shift));
       };
 
       // QK^T and the online softmax of one chunk: returns P^T packed as bf16 and
@@ -428,14 +412,15 @@ void decode_kernel(DecodeParams p) {
           for (int cg = 0; cg < kCGd; ++cg) acc[cg][dt] = mfma16x16x32(ch.v[dt], pf[cg], acc[cg][dt]);
       };
 
-      // One-page path (PG >= 32): a chunk's keys lie in one page.
-      if constexpr (kOnePage) {
+      {
         // chunks come in increasing order: the lane table moves forward when a
         // chunk's page lies past its 64 entries
         auto page_of = [&](int c) {
           const int lp = (cfirst + c * kChunk) >> shift;
-          if (lp - tab.lp0 >= kWave) load_lane_table(tab, pv, b, lp, last_lp, lane);
-          return __builtin_amdgcn_readlane(tab.page, lp - tab.lp0);
+          constexpr int kMore = kOnePage ? 0 : 1;  // further pages of the chunk
+          if (lp + kMore - tab.lp0 >= kWave) load_lane_table(tab, pv, b, lp, last_lp, lane);
+          return ChunkPages{__builtin_amdgcn_readlane(tab.page, lp - tab.lp0),
+                            __builtin_amdgcn_readlane(tab.page, lp - tab.lp0 + kMore)};
         };
         // this wave's chunks: c0, c0 + kCoop, ...
         const int nw = nchunks > c0 ? (nchunks - c0 + kCoop<kSplit> - 1) / kCoop<kSplit> : 0;
@@ -493,9 +478,9 @@ void decode_kernel(DecodeParams p) {
           Chunk ca, cb;
           auto issue_both = [&](int k, Chunk &ch) {
             const int cc = c0 + k * kCoop<kSplit>;
-            const int page = page_of(cc);
-            issue_k(cc, page, ch);
-            issue_v(cc, page, ch);
+            const ChunkPages pages = page_of(cc);
+            issue_k(cc, pages, ch);
+            issue_v(cc, pages, ch);
           };
           issue_both(0, ca);
           issue_both(min(1, nw - 1), cb);
@@ -538,9 +523,9 @@ void decode_kernel(DecodeParams p) {
         } else if (nw > 0) {
           Chunk ch;
           {
-            const int page = page_of(c0);
-            issue_k(c0, page, ch);
-            issue_v(c0, page, ch);
+            const ChunkPages pages = page_of(c0);
+            issue_k(c0, pages, ch);
+            issue_v(c0, pages, ch);
           }
           // The scheduling fences keep each chunk's loads behind the last use of
           // the registers they overwrite: one operand set, no loop-carried copies.
@@ -549,26 +534,18 @@ void decode_kernel(DecodeParams p) {
           u32x4 pf[kCGd];
           for (int k = 0; k < nw - 1; ++k) {
             const int cn = c0 + (k + 1) * kCoop<kSplit>;
-            const int next_page = page_of(cn);
+            const ChunkPages next = page_of(cn);
             f32x4 sa[kCGd], sb[kCGd];
             qk(ch, sa, sb);
             __builtin_amdgcn_sched_barrier(0);
-            issue_k(cn, next_page, ch);
+            issue_k(cn, next, ch);
             __builtin_amdgcn_sched_barrier(0);
             softmax(ch, sa, sb, pf);
             pv_update(ch, pf);
             __builtin_amdgcn_sched_barrier(0);
-            issue_v(cn, next_page, ch);
+            issue_v(cn, next, ch);
             __builtin_amdgcn_sched_barrier(0);
           }
-          scores(ch, pf);
-          pv_update(ch, pf);
-        }
-      } else {
-        for (int c = c0; c < nchunks; c += kCoop<kSplit>) {
-          Chunk ch;
-          u32x4 pf[kCGd];
-          issue(c, ch);
           scores(ch, pf);
           pv_update(ch, pf);
         }

@@ -39,6 +39,8 @@ __device__ __forceinline__ u32x4 ldnt128_global(const void *p) {
 // its 16 column maxima and sums.
 constexpr int kAStateBytes = 8 * kWave * 16 + 2 * kACols * 4;
 
+// kOnePage: a chunk's keys lie in one page (PG >= 32), else in two (PG = 16).
+template <bool kOnePage>
 __global__ __launch_bounds__(kWave * kAMaxWaves) void decode_append_kernel(DecodeParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_state[];
   const PoolView &pv = p.pool;
@@ -99,11 +101,12 @@ __global__ __launch_bounds__(kWave * kAMaxWaves) void decode_append_kernel(Decod
 
   const int app_page = page_of(pos >> shift);
 
-  // Lane offsets inside one 32-key chunk (PG >= 32: a chunk lies in one page):
-  // K half a (keys 8 i + j, j < 4, at MFMA row 4 i + j), half b 4 KiB on; the
-  // V^T block of dims 16 dt + r, keys 8 q .. +7.
-  const uint32_t koff = lane * 16;
-  const uint32_t voff = (r * 32 + 8 * q) * 2;
+  // Lane offsets inside a key block. PG >= 32: K half a (keys 8 i + j, j < 4, at
+  // MFMA row 4 i + j), half b 4 KiB on; the V^T block of dims 16 dt + r, keys
+  // 8 q .. +7. PG = 16: the same pieces of two 16-key blocks, 8 rows a slab.
+  constexpr uint32_t kslab = kOnePage ? 1024 : 512, vstep = kOnePage ? 1024 : 512;
+  const uint32_t koff = kOnePage ? lane * 16 : (q * 8 + (r & 7)) * 16;
+  const uint32_t voff = kOnePage ? (r * 32 + 8 * q) * 2 : r * 32 + (q & 1) * 16;
   const int key_a = 8 * (r >> 2) + (r & 3);  // this lane's K row key in half a (+4 in half b)
 
   float m = -FLT_MAX, lsum = 0.f;
@@ -113,24 +116,31 @@ __global__ __launch_bounds__(kWave * kAMaxWaves) void decode_append_kernel(Decod
 
   for (int c = wid; c < nchunks; c += nw) {
     const int cbase = cfirst + c * kAChunk;
-    const int page = page_of(cbase >> shift);
-    const int64_t pg64 = max(page, 0);
-    const char *kbase = reinterpret_cast<const char *>(pv.k_pool) +
-                        ((((pg64 * hkv + g) << shift) + (cbase & (pg - 1))) * kHeadDim) * 2;
-    const char *vbase = reinterpret_cast<const char *>(pv.v_pool) +
-                        ((((pg64 * hkv + g) << shift) << kHeadDimShift) +
-                         ((int64_t)((cbase & (pg - 1)) >> 5) << (5 + kHeadDimShift))) * 2;
+    // this lane's pages: the chunk's one, or of two 16-key ones those that hold
+    // its K rows (r >> 3) and its V keys (q >> 1); none past the last key's
+    int kpage = page_of(cbase >> shift), vpage = kpage;
+    if constexpr (!kOnePage) {
+      const int second = (cbase >> shift) < (pos >> shift) ? page_of((cbase >> shift) + 1) : -1;
+      kpage = r & 8 ? second : kpage;
+      vpage = q & 2 ? second : vpage;
+    }
+    auto page_base = [&](int page) {  // byte offset of the chunk's first block, or of the page
+      const int64_t ph = ((int64_t)max(page, 0) * hkv + g) << (shift + kHeadDimShift + 1);
+      return kOnePage ? ph + ((int64_t)((cbase & (pg - 1)) >> 5) << (5 + kHeadDimShift + 1)) : ph;
+    };
+    const char *kbase = reinterpret_cast<const char *>(pv.k_pool) + page_base(kpage);
+    const char *vbase = reinterpret_cast<const char *>(pv.v_pool) + page_base(vpage);
     // the new key (offset o of the last chunk; -1 elsewhere) comes from k_new / v_new
     const int o = pos - cbase < kAChunk ? pos - cbase : -1;
     const char *knew = reinterpret_cast<const char *>(p.k_new + kvrow + 8 * q);
     u32x4 ka[4], kbv[4], v[8];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      ka[t] = ldnt128_global(key_a == o ? knew + 64 * t : kbase + koff + 1024 * t);
-      kbv[t] = ldnt128_global(key_a + 4 == o ? knew + 64 * t : kbase + koff + 4096 + 1024 * t);
+      ka[t] = ldnt128_global(key_a == o ? knew + 64 * t : kbase + koff + kslab * t);
+      kbv[t] = ldnt128_global(key_a + 4 == o ? knew + 64 * t : kbase + koff + kslab * (4 + t));
     }
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) v[dt] = ldnt128_global(vbase + voff + dt * 1024);
+    for (int dt = 0; dt < 8; ++dt) v[dt] = ldnt128_global(vbase + voff + dt * vstep);
     uint32_t vn[8];
     if (o >= 0) {
 #pragma unroll
@@ -145,7 +155,7 @@ __global__ __launch_bounds__(kWave * kAMaxWaves) void decode_append_kernel(Decod
       sb = mfma16x16x32(kbv[t], qf[t], sb);
     }
     // lane holds keys cbase + 8 q .. +7 of column r
-    const uint32_t keep = page >= 0 ? key_range_bits(cbase + 8 * q, kb, pos) : 0u;
+    const uint32_t keep = vpage >= 0 ? key_range_bits(cbase + 8 * q, kb, pos) : 0u;
     float s[8];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -250,7 +260,7 @@ static int range_chunks(const DecodeParams &p) {
 }
 
 bool decode_append_fused(const DecodeParams &p) {
-  return p.nq == 1 && p.max_splits == 1 && p.pool.pg_shift >= 5 && range_chunks(p) <= kAMaxWaves;
+  return p.nq == 1 && p.max_splits == 1 && range_chunks(p) <= kAMaxWaves;
 }
 
 hipError_t launch_decode_append(const DecodeParams &p, hipStream_t stream) {
@@ -259,8 +269,9 @@ hipError_t launch_decode_append(const DecodeParams &p, hipStream_t stream) {
   const int hchunks = (p.group + kACols - 1) / kACols;
   const int64_t items = (int64_t)p.ns * p.hkv * hchunks;
   void *args[] = {const_cast<DecodeParams *>(&p)};
-  return hipLaunchKernel(reinterpret_cast<const void *>(decode_append_kernel), dim3((unsigned)items),
-                         dim3(kWave * nw), args, (size_t)nw * kAStateBytes, stream);
+  const void *kernel = p.pool.pg_shift >= 5 ? reinterpret_cast<const void *>(decode_append_kernel<true>)
+                                            : reinterpret_cast<const void *>(decode_append_kernel<false>);
+  return hipLaunchKernel(kernel, dim3((unsigned)items), dim3(kWave * nw), args, (size_t)nw * kAStateBytes, stream);
 }
 
 }  // namespace hswa

@@ -61,7 +61,7 @@ struct DecodeParams {
   float scale_log2;       // scale * log2(e)
   const uint16_t *k_new;  // decode step: the new token's K / V rows [ns][Hkv][D]
   const uint16_t *v_new;
-  // FULL split decode of one new token per sequence, PG >= 32: the kernel also
+  // FULL split decode of one new token per sequence: the kernel also
   // stores the token (k_new / v_new) in its slot and takes its key from them
   int32_t split_append;
 };
@@ -92,7 +92,7 @@ struct PrefillParams {
 hipError_t launch_kv_append(const AppendParams &p, hipStream_t stream);
 hipError_t launch_decode(const DecodeParams &p, hipStream_t stream);
 // Decode step with its append in the same launch (decode_append.hip): one
-// query per sequence, whole-range items of at most 8 chunks, PG >= 32.
+// query per sequence, whole-range items of at most 8 chunks.
 bool decode_append_fused(const DecodeParams &p);
 hipError_t launch_decode_append(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill(const PrefillParams &p, hipStream_t stream);

@@ -193,3 +193,30 @@ def test_decode_append_stack70_swa_layer(gpu_lib):
         kf = OA.bf16_bits_to_f64(np.concatenate([kh[b * n:(b + 1) * n], kn[b:b + 1]]))
         vf = OA.bf16_bits_to_f64(np.concatenate([vh[b * n:(b + 1) * n], vn[b:b + 1]]))
         assert_close(got[b], OA.decode(q[b], kf, vf, wl.window), f"stack70 SWA seq {b}")
+
+
+@pytest.mark.parametrize("kind,window,hq,hkv,lens", [
+    ("full", 0, 64, 8, [1, 2, 15, 16, 17, 31, 32, 33, 100, 255, 256]),      # the fused kernel
+    ("full", 0, 64, 8, [1, 257, 1009, 5000, 0, 2064]),                      # split: the token in either page of a chunk
+    ("full", 0, 64, 1, [300, 1040, 4097]),                                  # split, two head-group items
+    ("swa_paged", 100, 64, 8, [1, 16, 17, 99, 100, 131, 132, 777, 3000]),
+    ("swa", 400, 16, 16, [1, 399, 400, 417, 3000]),                         # too wide for the fused kernel
+])
+def test_decode_append_pg16(gpu_lib, kind, window, hq, hkv, lens):
+    """Pages of 16 keys: a 32-key chunk spans two of them."""
+    print(f"[decode-append pg16] {kind} W={window} {hq}/{hkv} {lens}", flush=True)
+    check(run_step(kind, window, 16, hq, hkv, lens, (308, window, hq, hkv)), f"{kind} W={window} PG=16")
+
+
+def test_decode_append_pg16_invalid_page(gpu_lib):
+    """One of a chunk's two pages invalid: its keys alone are left out."""
+    print("[decode-append pg16 invalid page]", flush=True)
+    lens = [5000, 4097, 300, 640]
+
+    def edit(table):
+        table[0, 4999 // 16] = -1    # the token's page
+        table[1, 2048 // 16] = -1    # the first page of a chunk
+        table[1, 2096 // 16] = 1 << 30  # the second page of another
+        table[3, 639 // 16] = -1
+
+    check(run_step("full", 0, 16, 64, 8, lens, (309,), table_edit=edit), "pg16 invalid page", oracle=False)
