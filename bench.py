@@ -55,14 +55,14 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 # measured again.
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
-                            "sha256": "4efb2e0317ba54068bb87f5b63665fe62b334af57391b9b2f4e4c24e94bc399f",
-                            "fetch_bytes": 8609292759, "write_bytes": 5573663},
+                            "sha256": "6af3853f278b171b94a93b6d45470a6410d7ac22a0ce05cc2cd0770acc2e15b1",
+                            "fetch_bytes": 8609206477, "write_bytes": 5574001},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
                      "sha256": "ba494e313af1e8dabd10fb160a420f29f4bc5c65788a36993632c3da1378c557",
-                     "fetch_bytes": 453002322, "write_bytes": 141376768},
+                     "fetch_bytes": 453229998, "write_bytes": 141347645},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
                     "sha256": "6efdd4bfa3ccfc2d92754704e8dc6c9f8a0041c8d251147d861c926c6a485d88",
-                    "fetch_bytes": 184782131, "write_bytes": 149697731},
+                    "fetch_bytes": 184783667, "write_bytes": 151860879},
 }
 
 

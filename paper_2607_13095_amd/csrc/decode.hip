@@ -51,6 +51,12 @@ __device__ __forceinline__ u32x4 ldnt128(const void *p) {
 constexpr int kChunk = 32;
 constexpr int kCols = 16;  // query heads per item (MFMA columns)
 constexpr int kMergeThreads = 256;
+// Up to this many rows a merged row has a workgroup of its own: with one wave
+// each, 64 rows of 65 pieces took as long as 8192 rows of few (1 x 16K, 64 heads:
+// 25.9 us a step against 23.9; 1 x 32K, 16 heads: 27.1 against 22.9); from about
+// 1024 rows on the further waves only cost (32 x 0.5-16K, 32 heads: 191.5
+// against 193).
+constexpr int kWideMergeRows = 512;
 constexpr float kRescaleLog2 = 8.f;  // lazy raise threshold of the running maximum (exp2 units)
 
 // Per-wave copy of a window of the block table: lane i holds the physical page
@@ -646,18 +652,23 @@ void decode_kernel(DecodeParams p) {
   }
 }
 
-// Log-sum-exp merge of the split partials: one wave per (sequence, query, head).
-// Lane j reads the log-sum-exp of pieces j, j+64, ...; the weights are then
+// Log-sum-exp merge of the split partials: kRowWaves waves per (sequence,
+// query, head) row, each taking every kRowWaves-th block of 16 pieces. Lane j reads the log-sum-exp of pieces j, j+64, ...; the weights are then
 // broadcast by readlane while the two half-waves accumulate even and odd
 // pieces, four output dims a lane (16-byte loads, 16 pieces in flight a step).
+template <int kRowWaves>
 __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeParams p) {
+  constexpr int kMergeWaves = kMergeThreads / kWave;
+  static_assert(kRowWaves == 1 || kRowWaves == kMergeWaves, "a row has one wave or its workgroup");
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t idx = (int64_t)blockIdx.x * (kMergeThreads / kWave) + (threadIdx.x / kWave);
+  const int wid = uni((int)(threadIdx.x / kWave));
+  const int rw = kRowWaves == 1 ? 0 : wid;  // wave of the row
+  const int64_t idx = (int64_t)blockIdx.x * (kMergeWaves / kRowWaves) + (kRowWaves == 1 ? wid : 0);
   if (idx >= (int64_t)p.ns * p.nq * p.hq) return;
   const int b = (int)(idx / ((int64_t)p.nq * p.hq));
   const int ctx = min(p.ctx_lens[b], p.max_ctx);
   const int half = lane >> 5, d4 = (lane & 31) * 4;
-  u32x2 *dst = reinterpret_cast<u32x2 *>(p.out + idx * kHeadDim + d4);
+  u32x2 *dst = reinterpret_cast<u32x2 *>(p.out + idx * kHeadDim + d4);  // (every wave of a row stores the same zeros)
   const u32x2 zero = {0u, 0u};
   if (ctx < 1) {
     if (half == 0) *dst = zero;
@@ -700,7 +711,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeParam
     const int s = s0 + lane;
     const float w = s < nsplit ? fast_exp2(lse[s] - mx) : 0.f;
     const int n = min(kWave, nsplit - s0);
-    for (int k0 = 0; k0 < n; k0 += 16) {
+    for (int k0 = 16 * rw; k0 < n; k0 += 16 * kRowWaves) {
       f32x4 v[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -724,6 +735,21 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeParam
   wsum = sum_xor32(wsum);
 #pragma unroll
   for (int i = 0; i < 4; ++i) o[i] = sum_xor32(o[i]);
+  if constexpr (kRowWaves > 1) {
+    __shared__ f32x4 s_o[kRowWaves][kWave / 2];
+    __shared__ float s_w[kRowWaves];
+    if (half == 0) s_o[rw][lane] = o;
+    if (lane == 0) s_w[rw] = wsum;
+    __syncthreads();
+    if (rw != 0) return;
+    wsum = 0.f;
+    o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kRowWaves; ++w) {
+      wsum += s_w[w];
+      o += s_o[w][lane & 31];
+    }
+  }
   const float inv = 1.f / wsum;
   if (half == 0) {
     u32x2 w2;
@@ -788,8 +814,10 @@ hipError_t launch_decode_cg(const DecodeParams &p0, hipStream_t stream) {
                  : launch_kernel(decode_kernel<true, false, kCGd>, grid, block, stream, p);
     if (e != hipSuccess) return e;
     const int64_t rows = (int64_t)p.ns * p.nq * p.hq;
-    const int per_block = kMergeThreads / kWave;
-    return launch_kernel(decode_merge_kernel, dim3((unsigned)((rows + per_block - 1) / per_block)),
+    constexpr int per_block = kMergeThreads / kWave;
+    if (rows <= kWideMergeRows)
+      return launch_kernel(decode_merge_kernel<per_block>, dim3((unsigned)rows), dim3(kMergeThreads), stream, p);
+    return launch_kernel(decode_merge_kernel<1>, dim3((unsigned)((rows + per_block - 1) / per_block)),
                          dim3(kMergeThreads), stream, p);
   }
   return one_page ? launch_kernel(decode_kernel<false, true, kCGd>, dim3((unsigned)items), block, stream, p)
