@@ -47,10 +47,13 @@ constexpr float kWLaneSumLimit = 4096.f;   // lane share of a row sum that raise
 struct WStage {
   u32x4 k[2], v[2];
   uint32_t keep;  // bit i: k[i] holds data (else zeros are stored); bits 8 + 8 i ..: the
-                  // elements (keys) of v[i] that hold data
+                  // elements (keys) of v[i] that hold data; all set inside the range
+  bool edge;      // some key of the chunk is out of range (or on an invalid page)
   bool vrow;      // v[] holds key rows (chunk keys), transposed at the store
 };
 
+// kPage16: 16-key pages, two of them a chunk; else a chunk lies in one page.
+template <bool kPage16>
 __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) void prefill_window_kernel(
     PrefillParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[kWBufs * kWBufBytes];
@@ -147,12 +150,29 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
   // block dt = idx >> 6 holds for lane r + 16 qq keys 8 qq .. +7 of dim
   // 16 dt + r.
   auto k_key = [](int idx) { return ((idx & 15) >> 2) * 8 + (idx >> 8) * 4 + (idx & 3); };
-  auto k_dim = [](int idx) { return ((idx >> 6) & 3) * 32 + ((idx >> 4) & 3) * 8; };
-  auto v_dim = [](int idx) { return (idx >> 6) * 16 + (idx & 15); };
   auto v_keys = [](int idx) { return ((idx >> 4) & 3) * 8; };
   const u32x4 zero = {0u, 0u, 0u, 0u};
-  // physical page of cached key j (-1: not cached or not valid), from the lane table
-  auto page_at = [&](int j) { return __shfl(tab, (j >> shift) - lp0, kWave); };
+  // physical page of logical page lp (-1: not cached or not valid), from the lane table
+  auto page_at = [&](int lp) { return __builtin_amdgcn_readlane(tab, min(lp - lp0, kWave - 1)); };
+  // Byte offsets of this thread's piece 0 and the steps to piece 1. A chunk's
+  // pieces sit at fixed offsets from a wave-uniform address, so a fetch takes a
+  // few vector instructions (forming each piece's address from its key, a page
+  // lookup and a 64-bit product each, took 53.9 us for 3 ragged chunks of
+  // 300-1200 tokens at W = 512, PG 16, 32 / 8 heads, against 49.1, and 230 for 4 x
+  // 2000 at PG 64, 64 / 8 heads, against 214).
+  // Pool blocks: the K block in LDS order and the [D][32] V block; with 16-key
+  // pages the same pieces of two blocks of 8-row slabs and [D][16].
+  const uint32_t v_dim = (uint32_t)((tid >> 6) * 16 + (tid & 15)), vq = (uint32_t)((tid >> 4) & 3);
+  const uint32_t pk_off = kPage16 ? (uint32_t)((tid >> 4) * 128 + (tid & 7) * 16) : (uint32_t)tid * 16;
+  const uint32_t pv_off = kPage16 ? v_dim * 32 + (vq & 1) * 16 : v_dim * 64 + vq * 16;
+  constexpr uint32_t p_step = kPage16 ? 2048 : 4096;
+  const bool ksecond = kPage16 && (tid & 8), vsecond = kPage16 && (vq & 2);  // on the chunk's second page
+  // Rows of k_new / v_new: K dims 32 t + 8 qq of chunk key k_key, V dims
+  // 8 (lane % 16) of chunk key 8 wave + lane / 16; piece 1 four keys on.
+  const uint32_t row_bytes = (uint32_t)hkv * (kHeadDim * 2);
+  const uint32_t nk_dim = (uint32_t)(((tid >> 6) & 3) * 64 + ((tid >> 4) & 3) * 16), nv_dim = (uint32_t)(lane & 15) * 16;
+  const uint32_t nk_off = (uint32_t)k_key(tid) * row_bytes + nk_dim;
+  const uint32_t nv_off = (uint32_t)(8 * wave + (lane >> 4)) * row_bytes + nv_dim;
   // The key range is cut at P into cached chunks, aligned to 32 absolute
   // positions (so that 8 consecutive keys of a V^T piece are 16 contiguous
   // bytes of one pool page), and chunks of the new keys, aligned to P. No chunk
@@ -171,50 +191,65 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
   auto fetch = [&](int c, WStage &st) {
     c = min(c, nch - 1);  // past the end: a repeat of the last chunk, never stored
     const int kb = chunk_base(c);
-    const uint16_t *ka[2], *va[2];
-    uint32_t keep = 0u;
-    if (c < ncached) {
-      // cached keys, any page size: K piece = dims k_dim of one key, V^T piece =
-      // keys 8 qq .. +7 (8-aligned, one page) of one dim
+    const bool cached = c < ncached;
+    const char *kbase, *vbase;  // wave-uniform, except that a lane picks its page of two
+    uint32_t ko[2], vo[2];
+    st.keep = 0xFFFF03u;
+    st.vrow = !cached;
+    if (cached) {
+      const int lp = kb >> shift;
+      const int pa = page_at(lp), pb = kPage16 ? page_at(lp + 1) : pa;
+      auto page_off = [&](int page) {
+        const int64_t ph = ((int64_t)max(page, 0) * hkv + g) << (shift + kHeadDimShift + 1);
+        return kPage16 ? ph : ph + ((int64_t)((kb & (pg - 1)) >> 5) << (5 + kHeadDimShift + 1));
+      };
+      const int64_t oa = page_off(pa), ob = page_off(pb);
+      kbase = reinterpret_cast<const char *>(pv.k_pool) + (ksecond ? ob : oa);
+      vbase = reinterpret_cast<const char *>(pv.v_pool) + (vsecond ? ob : oa);
+      ko[0] = pk_off;
+      vo[0] = pv_off;
+      ko[1] = pk_off + p_step;
+      vo[1] = pv_off + p_step;
+      st.edge = kb < klo || kb + kWChunk - 1 > chi || pa < 0 || pb < 0;
+      if (st.edge) {  // the pieces are all in their pages' bounds: only kept or not
+        uint32_t keep = 0u;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int idx = tid + kWThreads * i;
-        const int j = kb + k_key(idx);
-        const int kpage = page_at(j);
-        const bool in = j >= klo && j <= chi && kpage >= 0;
-        ka[i] = pv.k_pool + k_offset(pv, in ? kpage : 0, hkv, g, j & (pg - 1), k_dim(idx));
-        const int j0 = kb + v_keys(idx);
-        const int vpage = page_at(j0);
-        va[i] = pv.v_pool + v_offset(pv, vpage >= 0 ? vpage : 0, hkv, g, j0 & (pg - 1), v_dim(idx));
-        const uint32_t kv8 = vpage >= 0 ? key_range_bits(j0, klo, chi) : 0u;
-        keep |= (in ? 1u : 0u) << i;
-        keep |= kv8 << (8 + 8 * i);
+        for (int i = 0; i < 2; ++i) {
+          const int j = kb + k_key(tid + kWThreads * i), j0 = kb + v_keys(tid);
+          keep |= (j >= klo && j <= chi && (ksecond ? pb : pa) >= 0 ? 1u : 0u) << i;
+          keep |= ((vsecond ? pb : pa) >= 0 ? key_range_bits(j0, klo, chi) : 0u) << (8 + 8 * i);
+        }
+        st.keep = keep;
       }
-      st.vrow = false;
     } else {
-      // new keys: K rows as 16-byte pieces; V rows as 16-byte pieces of keys
-      // 8 wave + 4 i + lane / 16, dims 8 (lane % 16) .. +7 (transposed at the
-      // store). Keys past khi read row tok0 (in bounds) and are not kept.
+      const int64_t o = ((int64_t)(tok0 + kb - P) * hkv + g) * (kHeadDim * 2);
+      kbase = reinterpret_cast<const char *>(p.k_new) + o;
+      vbase = reinterpret_cast<const char *>(p.v_new) + o;
+      ko[0] = nk_off;
+      vo[0] = nv_off;
+      ko[1] = nk_off + 4 * row_bytes;
+      vo[1] = nv_off + 4 * row_bytes;
+      st.edge = kb < klo || kb + kWChunk - 1 > khi;
+      if (st.edge) {
+        // keys out of range read the chunk's last one in range (khi >= kb) and
+        // are not kept
+        uint32_t keep = 0u;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int idx = tid + kWThreads * i;
-        const int j = kb + k_key(idx);
-        const bool in = j >= klo && j <= khi;
-        ka[i] = p.k_new + ((int64_t)(tok0 + (in ? j - P : 0)) * hkv + g) * kHeadDim + k_dim(idx);
-        const int jv = kb + 8 * wave + 4 * i + (lane >> 4);
-        const bool inv = jv >= klo && jv <= khi;
-        va[i] = p.v_new + ((int64_t)(tok0 + (inv ? jv - P : 0)) * hkv + g) * kHeadDim + (lane & 15) * 8;
-        keep |= (in ? 1u : 0u) << i;
-        keep |= (inv ? 0xFFu : 0u) << (8 + 8 * i);
+        for (int i = 0; i < 2; ++i) {
+          const int jk = k_key(tid + kWThreads * i), jv = 8 * wave + 4 * i + (lane >> 4);
+          ko[i] = (uint32_t)min(jk, khi - kb) * row_bytes + nk_dim;
+          vo[i] = (uint32_t)min(jv, khi - kb) * row_bytes + nv_dim;
+          keep |= (kb + jk >= klo && kb + jk <= khi ? 1u : 0u) << i;
+          keep |= (kb + jv >= klo && kb + jv <= khi ? 0xFFu : 0u) << (8 + 8 * i);
+        }
+        st.keep = keep;
       }
-      st.vrow = true;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      st.k[i] = ldg128_global(ka[i]);
-      st.v[i] = ldg128_global(va[i]);
+      st.k[i] = ldg128_global(kbase + ko[i]);
+      st.v[i] = ldg128_global(vbase + vo[i]);
     }
-    st.keep = keep;
   };
   auto lds128 = [&](uint32_t off) { return reinterpret_cast<u32x4 *>(s_lds + off); };
   auto buf_off = [&](int buf) { return (uint32_t)__builtin_amdgcn_readfirstlane(buf * kWBufBytes); };
@@ -234,11 +269,12 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
   };
   auto store = [&](int buf, const WStage &st0) {
     WStage st = st0;
+    if (st.edge) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      st.k[i] = (st.keep >> i) & 1u ? st.k[i] : zero;
-      const uint32_t kv8 = (st.keep >> (8 + 8 * i)) & 0xFFu;
-      if (kv8 != 0xFFu) st.v[i] = keep_bf16x8(st.v[i], kv8);
+      for (int i = 0; i < 2; ++i) {
+        st.k[i] = (st.keep >> i) & 1u ? st.k[i] : zero;
+        st.v[i] = keep_bf16x8(st.v[i], (st.keep >> (8 + 8 * i)) & 0xFFu);
+      }
     }
     const uint32_t bo = buf_off(buf);
     *lds128(bo + 16 * tid) = st.k[0];
@@ -417,7 +453,8 @@ hipError_t launch_prefill_window(const PrefillParams &p, hipStream_t stream) {
   const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
   const int64_t pairs_per_xcd = ((int64_t)p.ns * p.hkv + kWXcds - 1) / kWXcds;
   const int64_t grid = pairs_per_xcd * ntq * kWXcds;
-  return launch_kernel(prefill_window_kernel, dim3((unsigned)grid), dim3(kWThreads), stream, p);
+  return launch_kernel(p.pool.pg_shift == 4 ? prefill_window_kernel<true> : prefill_window_kernel<false>,
+                       dim3((unsigned)grid), dim3(kWThreads), stream, p);
 }
 
 }  // namespace hswa

@@ -229,3 +229,28 @@ def test_prefill_split_table_larger_than_context(gpu_lib, prefix, chunk):
     ref = OA.prefill(OA.bf16_bits_to_f64(qb), OA.bf16_bits_to_f64(hist.k[0]), OA.bf16_bits_to_f64(hist.v[0]), prefix,
                      None)
     assert_close(to_f64(out), ref, f"{chunk} over {prefix}")
+
+
+@pytest.mark.parametrize("pg", [16, 32, 64, 256])
+@pytest.mark.parametrize("prefix", [480, 509])
+def test_prefill_window_pages(gpu_lib, pg, prefix):
+    """The windowed kernel over every kind of page, with an invalid ring entry
+    inside the window (a zero key and value) and NaN in unused slots."""
+    print(f"[prefill-window] PG={pg} P={prefix}", flush=True)
+    hq, hkv, d, window, chunk = 16, 2, 128, 200, 75
+    shape = hswa.Shape(hq, hkv, d, pg)
+    layer, kv = make_layer("swa", window, shape, [prefix + chunk], (207, pg))
+    hist = SeqHistory([prefix + chunk], hkv, d, 207, pg)
+    append_history(layer, shape, kv, hist, [0], [prefix])
+    qb = synth.normal_bf16((chunk, hq, d), 207, pg, synth.TAG_Q)
+    kf, vf = OA.bf16_bits_to_f64(hist.k[0]), OA.bf16_bits_to_f64(hist.v[0])
+    for bad in (None, 400 // pg):
+        if bad is not None:
+            kv.block_table[0, bad % hswa.ring_pages(window, pg)] = -1
+            kf[bad * pg:min(prefix, (bad + 1) * pg)] = 0
+            vf[bad * pg:min(prefix, (bad + 1) * pg)] = 0
+        out = torch.full((chunk, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        hswa.prefill(layer, shape, kv.cache, to_dev(qb), to_dev(hist.k[0][prefix:]), to_dev(hist.v[0][prefix:]),
+                     i32([0, chunk]), i32([prefix]), chunk, out)
+        torch.cuda.synchronize()
+        assert_close(to_f64(out), OA.prefill(OA.bf16_bits_to_f64(qb), kf, vf, prefix, window), f"PG {pg} bad {bad}")
