@@ -56,13 +56,13 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
                             "sha256": "6af3853f278b171b94a93b6d45470a6410d7ac22a0ce05cc2cd0770acc2e15b1",
-                            "fetch_bytes": 8609206477, "write_bytes": 5574001},
+                            "fetch_bytes": 8609199206, "write_bytes": 5574072},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
                      "sha256": "ba494e313af1e8dabd10fb160a420f29f4bc5c65788a36993632c3da1378c557",
-                     "fetch_bytes": 453229998, "write_bytes": 141347645},
+                     "fetch_bytes": 453294531, "write_bytes": 141434798},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
-                    "sha256": "6efdd4bfa3ccfc2d92754704e8dc6c9f8a0041c8d251147d861c926c6a485d88",
-                    "fetch_bytes": 184783667, "write_bytes": 151860879},
+                    "sha256": "2fc7264bd8e57f0207fa50361d0686b7aab043e00ee01a746e1cf1f1f838dda9",
+                    "fetch_bytes": 184855306, "write_bytes": 147648860},
 }
 
 
