@@ -166,14 +166,22 @@ class Shape:
         key = (self.num_q_heads, self.num_kv_heads, self.head_dim, self.page_size, self.scale)
         if getattr(self, "_ck", None) != key:
             self._c, self._ck = _Shape(*key), key
+            self._ref = ctypes.byref(self._c)
         return self._c
 
+    def ref(self):
+        self.c()
+        return self._ref
 
-def _ptr(t, name, dtypes, numel=None):
-    torch = _torch()
+
+def _ptr(t, name, dtypes, numel=0):
+    # one test of a well-formed tensor (a decode call of one sequence takes as
+    # long on the host as on the GPU), then which check failed
+    if isinstance(t, _TORCH.Tensor) and t.is_cuda and t.dtype in dtypes and t.is_contiguous() and t.numel() >= numel:
+        return t.data_ptr()
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _TORCH.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if not t.is_cuda:
         raise ValueError(f"{name} must live on the GPU")
@@ -181,29 +189,21 @@ def _ptr(t, name, dtypes, numel=None):
         raise TypeError(f"{name}: dtype {t.dtype} not in {dtypes}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if numel is not None and t.numel() < numel:
-        raise ValueError(f"{name} has {t.numel()} elements, needs {numel}")
-    return t.data_ptr()
+    raise ValueError(f"{name} has {t.numel()} elements, needs {numel}")
 
 
 _TORCH = None
+_BF16 = _I32 = _WS = ()  # accepted dtypes
 
 
 def _torch():
-    global _TORCH
+    global _TORCH, _BF16, _I32, _WS
     if _TORCH is None:
         import torch
 
+        _BF16, _I32, _WS = (torch.bfloat16,), (torch.int32,), (torch.uint8, torch.float32, torch.int32)
         _TORCH = torch
     return _TORCH
-
-
-def _bf16():
-    return (_torch().bfloat16,)
-
-
-def _i32():
-    return (_torch().int32,)
 
 
 V_BLOCK_MAX = 32
@@ -251,9 +251,15 @@ class Cache:
         # the tensors are fixed at construction: the struct is built (and the
         # tensors checked) once
         if getattr(self, "_c", None) is None:
-            self._c = _Cache(_ptr(self.k_pool, "k_pool", _bf16()), _ptr(self.v_pool, "v_pool", _bf16()),
-                             self.num_pages, _ptr(self.block_table, "block_table", _i32()), self.stride)
+            _torch()
+            self._c = _Cache(_ptr(self.k_pool, "k_pool", _BF16), _ptr(self.v_pool, "v_pool", _BF16),
+                             self.num_pages, _ptr(self.block_table, "block_table", _I32), self.stride)
+            self._ref = ctypes.byref(self._c)
         return self._c
+
+    def ref(self):
+        self.c()
+        return self._ref
 
 
 def _check_cache(shape: Shape, cache: Cache, ns: int):
@@ -277,12 +283,10 @@ def _stream(stream):
     torch = _torch()
     if stream is None:
         try:  # the current stream's handle without building a Stream object
-            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         except AttributeError:
-            return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+            return torch.cuda.current_stream().cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _check(status, where):
@@ -333,15 +337,14 @@ def kv_append(layer: Layer, shape: Shape, cache: Cache, k_new, v_new, cu_seqlens
               slot_mapping_out=None, stream=None):
     """Append k_new / v_new [T, Hkv, D] (bf16) to the pools; see hswa_kv_append."""
     torch = _torch()
-    ns = int(cu_seqlens.numel()) - 1
+    ns = cu_seqlens.numel() - 1
     t = int(k_new.shape[0]) if k_new.dim() else 0
     row = shape.num_kv_heads * shape.head_dim
-    args = (_ptr(k_new, "k_new", _bf16(), t * row), _ptr(v_new, "v_new", _bf16(), t * row),
-            _ptr(cu_seqlens, "cu_seqlens", _i32(), ns + 1), _ptr(start_pos, "start_pos", _i32(), ns))
+    args = (_ptr(k_new, "k_new", _BF16, t * row), _ptr(v_new, "v_new", _BF16, t * row),
+            _ptr(cu_seqlens, "cu_seqlens", _I32, ns + 1), _ptr(start_pos, "start_pos", _I32, ns))
     slots = _ptr(slot_mapping_out, "slot_mapping_out", (torch.int64,), t) if slot_mapping_out is not None else None
     _check_cache(shape, cache, ns)
-    sh, ca = shape.c(), cache.c()
-    st = load().hswa_kv_append(layer.c(), ctypes.byref(sh), ctypes.byref(ca), *args, ns, t, slots, _stream(stream))
+    st = load().hswa_kv_append(layer.c(), shape.ref(), cache.ref(), *args, ns, t, slots, _stream(stream))
     _check(st, "hswa_kv_append")
 
 
@@ -377,16 +380,17 @@ def prefill(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, cu_seqlen
     """Chunked prefill; q, out [T, Hq, D], k_new / v_new [T, Hkv, D]; see
     hswa_prefill and, for FULL calls with few query tiles, hswa_prefill_ws
     (their scratch is held for the length of the call only)."""
-    ns = int(cu_seqlens.numel()) - 1
+    _torch()
+    ns = cu_seqlens.numel() - 1
     t = int(q.shape[0])
     qrow, krow = shape.num_q_heads * shape.head_dim, shape.num_kv_heads * shape.head_dim
-    args = (_ptr(q, "q", _bf16(), t * qrow), _ptr(k_new, "k_new", _bf16(), t * krow),
-            _ptr(v_new, "v_new", _bf16(), t * krow), _ptr(cu_seqlens, "cu_seqlens", _i32(), ns + 1),
-            _ptr(prefix_lens, "prefix_lens", _i32(), ns))
-    o = _ptr(out, "out", _bf16(), t * qrow)
+    args = (_ptr(q, "q", _BF16, t * qrow), _ptr(k_new, "k_new", _BF16, t * krow),
+            _ptr(v_new, "v_new", _BF16, t * krow), _ptr(cu_seqlens, "cu_seqlens", _I32, ns + 1),
+            _ptr(prefix_lens, "prefix_lens", _I32, ns))
+    o = _ptr(out, "out", _BF16, t * qrow)
     _check_cache(shape, cache, ns)
     sh, ca = shape.c(), cache.c()
-    lib, lc, sp, cp, mc = load(), layer.c(), ctypes.byref(sh), ctypes.byref(ca), int(max_chunk_len)
+    lib, lc, sp, cp, mc = load(), layer.c(), shape.ref(), cache.ref(), int(max_chunk_len)
     need = lib.hswa_prefill_workspace_bytes(lc, sp, cp, ns, t, mc)
     ws = _prefill_scratch(need, stream) if need else None
     if ws is None:
@@ -405,23 +409,22 @@ def decode_multi_workspace_bytes(shape: Shape, ns: int, num_queries: int, max_co
 def decode_multi(layer: Layer, shape: Shape, cache: Cache, q, context_lens, max_context_len: int, out,
                  workspace=None, stream=None):
     """Multi-query decode; q, out [NS, nq, Hq, D]; see hswa_decode_multi."""
-    torch = _torch()
+    _torch()
     if q.dim() != 4:
         raise ValueError("q must be [NS, num_queries, Hq, D]")
     ns, nq = int(q.shape[0]), int(q.shape[1])
-    if int(context_lens.numel()) != ns:
+    if context_lens.numel() != ns:
         raise ValueError("one context length per sequence")
     row = nq * shape.num_q_heads * shape.head_dim
-    qp = _ptr(q, "q", _bf16(), ns * row)
-    cp = _ptr(context_lens, "context_lens", _i32(), ns)
-    o = _ptr(out, "out", _bf16(), ns * row)
+    qp = _ptr(q, "q", _BF16, ns * row)
+    cp = _ptr(context_lens, "context_lens", _I32, ns)
+    o = _ptr(out, "out", _BF16, ns * row)
     wp, wbytes = None, 0
     if workspace is not None:
-        wp = _ptr(workspace, "workspace", (torch.uint8, torch.float32, torch.int32))
+        wp = _ptr(workspace, "workspace", _WS)
         wbytes = workspace.numel() * workspace.element_size()
     _check_cache(shape, cache, ns)
-    sh, ca = shape.c(), cache.c()
-    st = load().hswa_decode_multi(layer.c(), ctypes.byref(sh), ctypes.byref(ca), qp, cp, ns, nq,
+    st = load().hswa_decode_multi(layer.c(), shape.ref(), cache.ref(), qp, cp, ns, nq,
                                   int(max_context_len), wp, wbytes, o, _stream(stream))
     _check(st, "hswa_decode_multi")
 
@@ -429,19 +432,18 @@ def decode_multi(layer: Layer, shape: Shape, cache: Cache, q, context_lens, max_
 def decode(layer: Layer, shape: Shape, cache: Cache, q, context_lens, max_context_len: int, out,
            workspace=None, stream=None):
     """Decode one query per sequence; q, out [NS, Hq, D]; see hswa_decode."""
-    torch = _torch()
-    ns = int(context_lens.numel())
+    _torch()
+    ns = context_lens.numel()
     qrow = shape.num_q_heads * shape.head_dim
-    qp = _ptr(q, "q", _bf16(), ns * qrow)
-    cp = _ptr(context_lens, "context_lens", _i32(), ns)
-    o = _ptr(out, "out", _bf16(), ns * qrow)
+    qp = _ptr(q, "q", _BF16, ns * qrow)
+    cp = _ptr(context_lens, "context_lens", _I32, ns)
+    o = _ptr(out, "out", _BF16, ns * qrow)
     wp, wbytes = None, 0
     if workspace is not None:
-        wp = _ptr(workspace, "workspace", (torch.uint8, torch.float32, torch.int32))
+        wp = _ptr(workspace, "workspace", _WS)
         wbytes = workspace.numel() * workspace.element_size()
     _check_cache(shape, cache, ns)
-    sh, ca = shape.c(), cache.c()
-    st = load().hswa_decode(layer.c(), ctypes.byref(sh), ctypes.byref(ca), qp, cp, ns, int(max_context_len), wp,
+    st = load().hswa_decode(layer.c(), shape.ref(), cache.ref(), qp, cp, ns, int(max_context_len), wp,
                             wbytes, o, _stream(stream))
     _check(st, "hswa_decode")
 
@@ -451,21 +453,20 @@ def decode_append(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, con
     """One decode step: store every sequence's new token (k_new / v_new
     [NS, Hkv, D]) at position context_lens[b] - 1, then decode q [NS, Hq, D]
     there; see hswa_decode_append."""
-    torch = _torch()
-    ns = int(context_lens.numel())
+    _torch()
+    ns = context_lens.numel()
     qrow, krow = shape.num_q_heads * shape.head_dim, shape.num_kv_heads * shape.head_dim
-    qp = _ptr(q, "q", _bf16(), ns * qrow)
-    kp = _ptr(k_new, "k_new", _bf16(), ns * krow)
-    vp = _ptr(v_new, "v_new", _bf16(), ns * krow)
-    cp = _ptr(context_lens, "context_lens", _i32(), ns)
-    o = _ptr(out, "out", _bf16(), ns * qrow)
+    qp = _ptr(q, "q", _BF16, ns * qrow)
+    kp = _ptr(k_new, "k_new", _BF16, ns * krow)
+    vp = _ptr(v_new, "v_new", _BF16, ns * krow)
+    cp = _ptr(context_lens, "context_lens", _I32, ns)
+    o = _ptr(out, "out", _BF16, ns * qrow)
     wp, wbytes = None, 0
     if workspace is not None:
-        wp = _ptr(workspace, "workspace", (torch.uint8, torch.float32, torch.int32))
+        wp = _ptr(workspace, "workspace", _WS)
         wbytes = workspace.numel() * workspace.element_size()
     _check_cache(shape, cache, ns)
-    sh, ca = shape.c(), cache.c()
-    st = load().hswa_decode_append(layer.c(), ctypes.byref(sh), ctypes.byref(ca), qp, kp, vp, cp, ns,
+    st = load().hswa_decode_append(layer.c(), shape.ref(), cache.ref(), qp, kp, vp, cp, ns,
                                    int(max_context_len), wp, wbytes, o, _stream(stream))
     _check(st, "hswa_decode_append")
 
@@ -474,14 +475,14 @@ def decode_noalloc(layer: Layer, shape: Shape, cache: Cache, q, context_lens, ma
                    stream=None):
     """Decode without a workspace (the library's fixed device array holds the
     split partials); q, out [NS, Hq, D]; see hswa_decode_noalloc."""
-    ns = int(context_lens.numel())
+    _torch()
+    ns = context_lens.numel()
     qrow = shape.num_q_heads * shape.head_dim
-    qp = _ptr(q, "q", _bf16(), ns * qrow)
-    cp = _ptr(context_lens, "context_lens", _i32(), ns)
-    o = _ptr(out, "out", _bf16(), ns * qrow)
+    qp = _ptr(q, "q", _BF16, ns * qrow)
+    cp = _ptr(context_lens, "context_lens", _I32, ns)
+    o = _ptr(out, "out", _BF16, ns * qrow)
     _check_cache(shape, cache, ns)
-    sh, ca = shape.c(), cache.c()
-    st = load().hswa_decode_noalloc(layer.c(), ctypes.byref(sh), ctypes.byref(ca), qp, cp, ns, int(max_context_len),
+    st = load().hswa_decode_noalloc(layer.c(), shape.ref(), cache.ref(), qp, cp, ns, int(max_context_len),
                                     o, _stream(stream))
     _check(st, "hswa_decode_noalloc")
 
