@@ -8,10 +8,16 @@
 // window of a few hundred keys most of its work is prologue and masked pairs.
 // This kernel instead gives each workgroup 128 query rows (4 waves x 32 rows,
 // a row = a (position, query head) pair of one KV head's GQA group), streams
-// the workgroup's key range W + 128 / G - 1 through a ring of four 32-key
-// chunk buffers (64 KiB, so two workgroups share a CU and hide each other's
-// memory latency) with the global loads two chunks ahead, and lets each wave
-// skip the chunks that lie wholly outside the windows of its own rows.
+// the workgroup's key range W + 128 / G - 1 through two 32-key chunk buffers
+// (32 KiB) with the global loads one chunk ahead, and lets each wave skip the
+// chunks that lie wholly outside the windows of its own rows.
+//
+// A wave's chunk is a serial chain (LDS reads, QK^T, softmax, PV, a barrier), so
+// the kernel is bound by how many waves share a SIMD: three (168 VGPRs, three
+// workgroups a CU) against two with four buffers, two register stages and the V
+// operands read ahead: 3 ragged chunks of 300-1200 tokens, W = 512, PG 16,
+// 32 / 8 heads 49.2 -> 41.4 us (0.52 PFLOP/s); 4 x 2000, 64 / 8 heads, W = 512
+// 216 -> 186, W = 256 138 -> 117.
 //
 // Per 32-key chunk and wave (bf16 MFMA, fp32 accumulate):
 //   S^T[key][row] = K[key][:] . Q[row][:]     (Q held in registers)
@@ -37,7 +43,7 @@ constexpr int kWThreads = 256;
 constexpr int kWWaves = kWThreads / kWave;  // 4
 constexpr int kWRows = kWWaves * 32;         // query rows per workgroup
 constexpr int kWChunk = 32;                  // keys per chunk
-constexpr int kWBufs = 4;                    // chunks c, c + 1 ready; c + 2 being stored; c - 1 done
+constexpr int kWBufs = 2;                    // chunk c being read, c + 1 being stored
 constexpr int kWKBytes = kWChunk * kHeadDim * 2;  // 8 KiB of K per chunk
 constexpr int kWBufBytes = 2 * kWKBytes;          // K, then V^T
 constexpr int kWXcds = 8;
@@ -54,7 +60,7 @@ struct WStage {
 
 // kPage16: 16-key pages, two of them a chunk; else a chunk lies in one page.
 template <bool kPage16>
-__global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) void prefill_window_kernel(
+__global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(3))) void prefill_window_kernel(
     PrefillParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[kWBufs * kWBufBytes];
 
@@ -112,24 +118,22 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
     }
   }
 
-  // Q^T operands and the window of each of this lane's columns.
+  const int gshift = __builtin_ctz(G);  // groups are powers of two
+
+  // Q^T operands of each of this lane's columns.
   u32x4 qf[kWCG][4];
-  int cpos[kWCG], clo[kWCG];
-  bool cval[kWCG];
 #pragma unroll
   for (int cg = 0; cg < kWCG; ++cg) {
     const int row = wave * (16 * kWCG) + cg * 16 + r;
     const int po = row / G, head = row - po * G;
-    cval[cg] = q0 + po <= q1;
-    cpos[cg] = P + q0 + po;
-    clo[cg] = max(0, cpos[cg] - W + 1);
-    const int64_t tok = tok0 + q0 + (cval[cg] ? po : 0);
+    const bool cval = q0 + po <= q1;
+    const int64_t tok = tok0 + q0 + (cval ? po : 0);
     const uint16_t *qrow = p.q + (tok * hq + (int64_t)g * G + head) * kHeadDim;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const u32x4 v = ldg128(qrow + 32 * t + 8 * q);
       const u32x4 z = {0u, 0u, 0u, 0u};
-      qf[cg][t] = cval[cg] ? v : z;
+      qf[cg][t] = cval ? v : z;
     }
   }
   // This wave's rows: positions po_lo .. po_hi of the tile (none if po_lo is
@@ -255,7 +259,7 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
   auto buf_off = [&](int buf) { return (uint32_t)__builtin_amdgcn_readfirstlane(buf * kWBufBytes); };
   // V^T bytes of dims 8 (lane % 16) + 2 (lane / 16) and + 1, keys 8 wave .. +7
   const uint32_t st_vrow = kWKBytes + ((((8 * (lane & 15)) >> 4) * 64 + ((8 * (lane & 15) + 2 * (lane >> 4)) & 15) +
-                                        16 * wave) * 16);
+                                        16 * wave) * 16) + (lane & 2 ? 16 : 0);
   // 4 x 4 transpose of dwords across the lanes l, l ^ 16, l ^ 32, l ^ 48.
   auto transpose4 = [&](const u32x4 &t, uint32_t (&w)[4]) {
     const auto a = __builtin_amdgcn_permlane32_swap(t[0], t[2], false, false);
@@ -295,8 +299,12 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
         lo[j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x05040100u);
         hi[j] = __builtin_amdgcn_perm(w[2 * j + 1], w[2 * j], 0x07060302u);
       }
-      *lds128(bo + st_vrow) = lo;
-      *lds128(bo + st_vrow + 16) = hi;
+      // Lanes whose block dt is odd store their two dims the other way round:
+      // the dims of a store's lanes are 8 apart and would meet two of the sixteen
+      // 16-byte bank groups, so they meet four (41.4 -> 39.2 us as above).
+      const u32x4 v0 = lane & 2 ? hi : lo, v1 = lane & 2 ? lo : hi;
+      *lds128(bo + st_vrow) = v0;
+      *lds128(bo + (st_vrow ^ 16)) = v1;
     }
   };
 
@@ -334,17 +342,18 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
         sc[1][cg] = mfma16x16x32(kbv, qf[cg][t], sc[1][cg]);
       }
     }
-    // V^T operands, read while the scores are formed
-    u32x4 vf[8];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) vf[dt] = *lds128(a + kWKBytes + 1024 * dt);
     if (!(kb >= wint_lo && kb + kWChunk - 1 <= min(wint_hi, kend))) {
       // this lane's keys are kb + 8 q + e, e = 4 ab + i
+      // (the rows' positions are formed here, in the masked chunks only: kept
+      // across the loop they would cost registers)
+      int row0 = wave * (16 * kWCG) + r;
+      asm volatile("" : "+v"(row0));
       const int j0 = kb + 8 * q;
 #pragma unroll
       for (int cg = 0; cg < kWCG; ++cg) {
-        const int lo_e = max(clo[cg] - j0, 0);
-        const int hi_e = min(min(cpos[cg], kend) - j0, 7);
+        const int cpos = pfirst + ((row0 + 16 * cg) >> gshift);
+        const int lo_e = max(cpos - W + 1 - j0, 0);
+        const int hi_e = min(min(cpos, kend) - j0, 7);
         const uint32_t bits = hi_e < lo_e ? 0u : ((2u << hi_e) - 1u) & ~((1u << lo_e) - 1u);
 #pragma unroll
         for (int ab = 0; ab < 2; ++ab)
@@ -370,6 +379,7 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
         }
       }
     };
+    __builtin_amdgcn_sched_barrier(0);
     exps();
     bool raise = false;
 #pragma unroll
@@ -391,40 +401,36 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
     }
 #pragma unroll
     for (int cg = 0; cg < kWCG; ++cg) lsum[cg] += ts[cg];
+    // V^T operands in two batches of four (fewer registers live at once)
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt)
+    for (int h = 0; h < 2; ++h) {
+      u32x4 vf[4];
 #pragma unroll
-      for (int cg = 0; cg < kWCG; ++cg) acc[cg][dt] = mfma16x16x32(vf[dt], pf[cg], acc[cg][dt]);
+      for (int d4 = 0; d4 < 4; ++d4) vf[d4] = *lds128(a + kWKBytes + 1024 * (4 * h + d4));
+#pragma unroll
+      for (int d4 = 0; d4 < 4; ++d4)
+#pragma unroll
+        for (int cg = 0; cg < kWCG; ++cg) acc[cg][4 * h + d4] = mfma16x16x32(vf[d4], pf[cg], acc[cg][4 * h + d4]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 
-  // ---- chunk loop: chunk c is computed from buffer c % 4. Two register
-  // stages carry the global loads two chunks ahead: chunk c + 2, loaded during
-  // chunk c - 2 (or before the loop), is stored into buffer (c + 2) % 4 after
-  // chunk c's compute (chunk c - 2 read that buffer, and the barrier that
-  // opens chunk c - 1 ended those reads), and chunk c + 4's loads go out into
-  // the stage it frees.
-  // Every step issues the same loads (one fetch), so that the wait before a
-  // stage's store counts exactly the other stage's loads.
-  WStage st[2];
-  fetch(0, st[0]);
-  fetch(1, st[1]);
-  store(0, st[0]);
-  fetch(2, st[0]);
-  if (nch > 1) store(1, st[1]);
-  fetch(3, st[1]);
-  auto step = [&](int c, WStage &s2) {  // s2: the stage holding chunk c + 2
-    const int kb = chunk_base(min(c, nch - 1));
+  // ---- chunk loop: chunk c is computed from buffer c % 2 while chunk c + 1,
+  // loaded a step ahead, is stored into the other one (chunk c - 1's, whose
+  // reads the barrier that opens the step ended) and chunk c + 2's loads go out.
+  WStage st;
+  {
+    WStage s0;  // both in flight (the accumulators are not live yet)
+    fetch(0, s0);
+    fetch(1, st);
+    store(0, s0);
+  }
+  for (int c = 0; c < nch; ++c) {
+    const int kb = chunk_base(c);
     __syncthreads();
-    if (c < nch && wact && kb + kWChunk - 1 >= wklo && kb <= wkhi) chunk(c % kWBufs, kb, c < ncached ? chi : khi);
-    if (c + 2 < nch) store((c + 2) % kWBufs, s2);
-    fetch(c + 4, s2);
-  };
-  // unrolled by two, both steps unconditional (a step past the end only
-  // fetches), so each stage is named statically and the newest loads are
-  // always the other stage's
-  for (int c = 0; c < nch; c += 2) {
-    step(c, st[0]);
-    step(c + 1, st[1]);
+    if (wact && kb + kWChunk - 1 >= wklo && kb <= wkhi) chunk(c % kWBufs, kb, c < ncached ? chi : khi);
+    if (c + 1 < nch) store((c + 1) % kWBufs, st);
+    fetch(c + 2, st);
   }
 
   // ---- normalise and write ----
@@ -434,14 +440,15 @@ __global__ __launch_bounds__(kWThreads) __attribute__((amdgpu_waves_per_eu(2))) 
     const float inv = 1.f / l;
     const int row = wave * (16 * kWCG) + cg * 16 + r;
     const int po = row / G, head = row - po * G;
-    uint16_t *orow = p.out + ((int64_t)(tok0 + q0 + (cval[cg] ? po : 0)) * hq + (int64_t)g * G + head) * kHeadDim;
+    const bool cval = q0 + po <= q1;
+    uint16_t *orow = p.out + ((int64_t)(tok0 + q0 + (cval ? po : 0)) * hq + (int64_t)g * G + head) * kHeadDim;
     u32x2 w[8];
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) {
       w[dt][0] = pack_bf16x2(acc[cg][dt][0] * inv, acc[cg][dt][1] * inv);
       w[dt][1] = pack_bf16x2(acc[cg][dt][2] * inv, acc[cg][dt][3] * inv);
     }
-    store_out_row(orow, w, q, cval[cg]);
+    store_out_row(orow, w, q, cval);
   }
 }
 
