@@ -165,13 +165,17 @@ class Shape:
     def c(self):
         key = (self.num_q_heads, self.num_kv_heads, self.head_dim, self.page_size, self.scale)
         if getattr(self, "_ck", None) != key:
-            self._c, self._ck = _Shape(*key), key
+            self._c = _Shape(*key)
             self._ref = ctypes.byref(self._c)
+            self._ck = key  # last: another thread that sees the key finds both
         return self._c
 
     def ref(self):
         self.c()
         return self._ref
+
+    def __getstate__(self):  # a copy or pickle builds its own (a byref cannot be pickled)
+        return {k: v for k, v in self.__dict__.items() if k not in ("_c", "_ck", "_ref")}
 
 
 def _ptr(t, name, dtypes, numel=0):
@@ -252,9 +256,10 @@ class Cache:
         # tensors checked) once
         if getattr(self, "_c", None) is None:
             _torch()
-            self._c = _Cache(_ptr(self.k_pool, "k_pool", _BF16), _ptr(self.v_pool, "v_pool", _BF16),
-                             self.num_pages, _ptr(self.block_table, "block_table", _I32), self.stride)
-            self._ref = ctypes.byref(self._c)
+            c = _Cache(_ptr(self.k_pool, "k_pool", _BF16), _ptr(self.v_pool, "v_pool", _BF16),
+                       self.num_pages, _ptr(self.block_table, "block_table", _I32), self.stride)
+            self._ref = ctypes.byref(c)
+            self._c = c  # last: another thread that sees it finds the reference too
         return self._c
 
     def ref(self):

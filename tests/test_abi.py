@@ -3,8 +3,10 @@ include/hswa.h declares, its host helpers agree bit-exactly with the layout
 oracle, and argument validation returns the documented status codes before
 any device work (no GPU is touched by these tests)."""
 
+import copy
 import ctypes
 import os
+import pickle
 import re
 
 import numpy as np
@@ -257,3 +259,11 @@ def test_decode_append_validation():
     assert call(hswa._Layer(1, 0), _cache(), 2, 100) == -1            # SWA window < 1
     assert call(FULL, _cache(stride=600), 64, 32769) == -1            # split FULL without a workspace
     assert call(SWA128, _cache(stride=3), 0, 100) == 0                # nothing to do
+
+
+def test_used_shape_can_be_copied_and_pickled():
+    shape = hswa.Shape(64, 8, 128, 16, 0.5)
+    shape.ref()
+    for other in (copy.copy(shape), copy.deepcopy(shape), pickle.loads(pickle.dumps(shape))):
+        other.page_size = 64
+        assert (other.c().page_size, shape.c().page_size, other.c().scale) == (64, 16, 0.5)
