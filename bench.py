@@ -55,8 +55,8 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 # measured again.
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
-                            "sha256": "6af3853f278b171b94a93b6d45470a6410d7ac22a0ce05cc2cd0770acc2e15b1",
-                            "fetch_bytes": 8609199206, "write_bytes": 5574072},
+                            "sha256": "6ffdde6260ad42115a25fb27f49316b6e38d2c7b59e7ef547d3f414bdaa6b178",
+                            "fetch_bytes": 8609247198, "write_bytes": 5574727},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
                      "sha256": "ba494e313af1e8dabd10fb160a420f29f4bc5c65788a36993632c3da1378c557",
                      "fetch_bytes": 453294531, "write_bytes": 141434798},
