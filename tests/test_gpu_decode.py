@@ -173,3 +173,15 @@ def test_decode_full_one_long_sequence_many_pieces(gpu_lib):
     print(f"[decode-full-one-long] split_len={sl}", flush=True)
     gpu, ref = run_decode("full", 0, 64, 64, 8, ctxs, (208,))
     assert_close(gpu, ref, "full one long sequence")
+
+
+@pytest.mark.parametrize("pg", [16, 64])
+@pytest.mark.parametrize("ctx", [8191, 8192, 28671, 28672])
+def test_decode_full_few_spans(gpu_lib, pg, ctx):
+    """Spans dealt to the workgroups one at a time, or four neighbours to each: on
+    256 compute units of four waves, 8 heads and spans of 256 keys, a workgroup
+    gets its second span from 8193 keys on, and neighbours from 28673 on."""
+    print(f"[decode-full-few-spans] pg={pg} ctx={ctx}", flush=True)
+    assert hswa.decode_split_len(hswa.Shape(16, 8, 128, pg), 1, ctx + 1) == 256
+    gpu, ref = run_decode("full", 0, pg, 16, 8, [ctx], (212, pg, ctx))
+    assert_close(gpu, ref, f"few spans pg={pg} ctx={ctx}")
