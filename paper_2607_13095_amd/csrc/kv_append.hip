@@ -8,26 +8,28 @@
 // Bound by moving the rows: every row is read once and written once. What
 // decides the rate is the width of the V stores, since a V block is transposed
 // ([D][B] keys) and a token's column in it is 128 scattered 2-byte elements.
-// The work is therefore cut along the pool's blocks, not along the batch: for
-// each aligned run of 32 positions of one sequence and KV head, one workgroup
-// reads its rows (64-byte runs of 16 rows per load instruction), transposes V
-// in registers with lane swaps, and writes whole 16-byte pieces, the K block as
-// contiguous 1 KiB runs and V as full 64-byte rows, whatever the sequences'
-// alignment in the batch. Only the first and last 8 keys of a sequence's append
-// can be partial pieces (2-byte stores). Cutting at 8 tokens of the batch
-// instead left 2-byte stores for every sequence whose position and batch
-// offset differ modulo 8.
+// Long sequences are therefore cut along the pool's blocks, not along the batch:
+// for each aligned run of 32 positions of one sequence and KV head, one
+// workgroup reads its rows (64-byte runs of 16 rows per load instruction),
+// transposes V in registers with lane swaps, and writes whole 16-byte pieces,
+// the K block as contiguous 1 KiB runs and V as full 64-byte rows, whatever the
+// sequences' alignment in the batch; only the first and last 8 keys of such an
+// append can be partial pieces (2-byte stores).
 // 12.3K tokens in 8 sequences at unaligned positions, 8 heads, PG 64 (101 MB
-// read and written): 92 -> 25 us, 4.0 TB/s (a large device copy: 4.7).
-// Sequences of fewer than 16 new tokens (a decode step's single token) are
-// scattered token by token, all tokens of a tile at once.
+// read and written): 92 us cut at 8 tokens of the batch, 25 by runs, 4.0 TB/s
+// (a large device copy: 4.9).
+// Sequences of fewer than 8 new tokens of a batch of longer ones are scattered
+// token by token. Calls of few tokens a sequence take 8-token tiles, which
+// scatter them too, except that eight tokens on 8 aligned slots in a row go out
+// as one 16-byte V store a dim (see append_tile for which call takes which tile).
+#include "append_grid.h"
 #include "hswa_common.h"
 #include "hswa_launch.h"
 
 namespace hswa {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kAppendThreads;
 constexpr int kLdsSeqs = 4096;  // batches up to this size search cu_seqlens in LDS
 constexpr int kRun = 32;        // positions of an aligned run
 
@@ -81,8 +83,9 @@ __device__ __forceinline__ void transpose4(const u32x4 &t, uint32_t *w) {
 // 8-token tiles scatter every sequence.
 template <int kTok>
 __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
-  // sequences of at least this many new tokens are written by runs
-  constexpr int kLong = kTok == kRun ? kRun / 2 : INT32_MAX;
+  // sequences of at least this many new tokens are written by runs (8 against
+  // 16: 4096 + 64 x 12 tokens 11.0 us against 14.1)
+  constexpr int kLong = kTok == 8 ? INT32_MAX : 8;
   __shared__ int32_t s_cu[kLdsSeqs + 1];
   const PoolView &pv = p.pool;
   const int hkv = p.hkv;
@@ -94,23 +97,23 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int pg = 1 << pv.pg_shift;
 
-  // The pieces of a short sequence's rows this thread stores. An 8-token tile
-  // (mostly single tokens) loads them at once, next to the lengths and the
-  // table, so that only the stores wait for the slots.
-  constexpr bool kEarly = kTok == 8;
-  constexpr int kSK = (kTok * 16 + kThreads - 1) / kThreads, kSV = kTok * kHeadDim / kThreads;
-  u32x4 ek[kSK];
-  uint16_t ev[kSV];
-  if constexpr (kEarly) {
+  // An 8-token tile loads its rows at once, next to the lengths and the table,
+  // so that only the stores wait for the slots: waves 0 and 1 a 16-byte piece
+  // of a K row a thread, waves 2 and 3 one dim of all 8 V rows.
+  constexpr bool kTile8 = kTok == 8;
+  constexpr int kSK = (kTok * 16 + kThreads - 1) / kThreads, kSV = kTok * kHeadDim / kThreads;  // pieces a thread
+  [[maybe_unused]] u32x4 ek = {0u, 0u, 0u, 0u};
+  [[maybe_unused]] uint16_t ev[8] = {};
+  if constexpr (kTile8) {
+    if (wave < 2) {
+      const int tk = min(t0 + (tid >> 4), p.total_tokens - 1);
+      ek = ldg128(p.k_new + ((int64_t)tk * hkv + g) * kHeadDim + (tid & 15) * 8);
+    } else {
 #pragma unroll
-    for (int i = 0; i < kSK; ++i) {
-      const int tk = min(t0 + (((tid + kThreads * i) >> 4) & (kTok - 1)), p.total_tokens - 1);
-      ek[i] = ldg128(p.k_new + ((int64_t)tk * hkv + g) * kHeadDim + (tid & 15) * 8);
-    }
-#pragma unroll
-    for (int i = 0; i < kSV; ++i) {
-      const int tk = min(t0 + ((tid + kThreads * i) >> kHeadDimShift), p.total_tokens - 1);
-      ev[i] = p.v_new[((int64_t)tk * hkv + g) * kHeadDim + (tid & (kHeadDim - 1))];
+      for (int i = 0; i < 8; ++i) {
+        const int tk = min(t0 + i, p.total_tokens - 1);
+        ev[i] = p.v_new[((int64_t)tk * hkv + g) * kHeadDim + tid - kHeadDim];
+      }
     }
   }
 
@@ -176,32 +179,65 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
     if (slots && tok_ok) p.slot_out[t] = slot;
   }
 
-  // Short sequences: K rows as sixteen 16-byte pieces, V element by element.
+  const int64_t sslot = scatter ? slot : -1;
+  if constexpr (kTile8) {
+    if (smask == 0) return;
+    if (wave < 2) {
+      const int64_t s = __shfl(sslot, tid >> 4, kWave);
+      if (s >= 0)
+        stg128(pv.k_pool + k_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), (tid & 15) * 8), ek);
+      return;
+    }
+    // Eight tokens on 8 aligned slots in a row: one 16-byte V store a dim. (A
+    // chunk or a few tokens a sequence at aligned positions; without it 2048
+    // aligned tokens among 256 single ones took 17.8 us instead of 10.6, and
+    // 256 x 8 aligned tokens 15.3 instead of 7.7.)
+    const int d = tid - kHeadDim;
+    const int64_t s0 = __shfl(sslot, 0, kWave);
+    const uint64_t in_row = __builtin_amdgcn_ballot_w64(lane < 8 && sslot == s0 + lane);
+    if (in_row == 0xFFu && s0 >= 0 && (s0 & 7) == 0) {
+      u32x4 w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = ev[2 * i] | ((uint32_t)ev[2 * i + 1] << 16);
+      stg128(pv.v_pool + v_offset(pv, s0 >> pv.pg_shift, hkv, g, (int)(s0 & (pg - 1)), d), w);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int64_t s = __shfl(sslot, i, kWave);
+      if (s >= 0) pv.v_pool[v_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), d)] = ev[i];
+    }
+    return;
+  }
+
+  // Short sequences of a larger tile: K rows as sixteen 16-byte pieces, V
+  // element by element, all loads ahead of the stores.
   if (smask != 0) {
-    const int64_t sslot = scatter ? slot : -1;
+    u32x4 ks[kSK];
+    uint16_t vs[kSV];
+    const int ktok = tid >> 4, vtok = wave >> 1;  // of piece 0; a later one's is 16 (K) or 2 (V) tokens on
+    const uint16_t *krow = p.k_new + ((int64_t)t0 * hkv + g) * kHeadDim + (tid & 15) * 8;
+    const uint16_t *vrow = p.v_new + ((int64_t)t0 * hkv + g) * kHeadDim + (tid & (kHeadDim - 1));
+    const int64_t row = (int64_t)hkv * kHeadDim;
+#pragma unroll
+    for (int i = 0; i < kSK; ++i)
+      if ((smask >> (ktok + 16 * i)) & 1u) ks[i] = ldg128(krow + (ktok + 16 * i) * row);
+#pragma unroll
+    for (int i = 0; i < kSV; ++i)
+      if ((smask >> (vtok + 2 * i)) & 1u) vs[i] = vrow[(vtok + 2 * i) * row];
 #pragma unroll
     for (int i = 0; i < kSK; ++i) {
-      const int idx = tid + kThreads * i;
-      const int tok = (idx >> 4) & (kTok - 1), c = idx & 15;
-      const int64_t s = __shfl(sslot, tok, kWave);
-      if (idx < kTok * 16 && s >= 0) {
-        const u32x4 v = kEarly ? ek[i] : ldg128(p.k_new + ((int64_t)(t0 + tok) * hkv + g) * kHeadDim + c * 8);
-        stg128(pv.k_pool + k_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), c * 8), v);
-      }
+      const int64_t s = __shfl(sslot, ktok + 16 * i, kWave);
+      if (s >= 0) stg128(pv.k_pool + k_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), (tid & 15) * 8), ks[i]);
     }
 #pragma unroll
     for (int i = 0; i < kSV; ++i) {
-      const int idx = tid + kThreads * i;
-      const int tok = idx >> kHeadDimShift, d = idx & (kHeadDim - 1);
-      const int64_t s = __shfl(sslot, tok, kWave);
-      if (s >= 0) {
-        const uint16_t v = kEarly ? ev[i] : p.v_new[((int64_t)(t0 + tok) * hkv + g) * kHeadDim + d];
-        pv.v_pool[v_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), d)] = v;
-      }
+      const int64_t s = __shfl(sslot, vtok + 2 * i, kWave);
+      if (s >= 0)
+        pv.v_pool[v_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), tid & (kHeadDim - 1))] = vs[i];
     }
   }
 
-  if constexpr (kTok != kRun) return;
   // Long sequences: the runs that start in this tile (a sequence's first token,
   // or a position that is a multiple of kRun).
   const bool two = pv.pg_shift == 4;
@@ -292,22 +328,10 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
 
 hipError_t launch_kv_append(const AppendParams &p, hipStream_t stream) {
   if (p.total_tokens <= 0) return hipSuccess;
-  // Chunks: 32-token tiles, a run each. A few tokens per sequence (decode
-  // steps), or a few in all, are bound by the launch and a chain of loads:
-  // 8-token tiles, scattered, put them on more compute units with the rows'
-  // loads ahead of the slots (8 heads, replayed as a graph, us per call, runs
-  // against scatter: 16 sequences x 16 tokens 5.2 / 3.8, 1 x 100 4.7 / 3.7,
-  // 32 x 12 8.0 / 6.0, 1 x 300 4.8 / 5.2, 4 x 2048 into a ring 6.1 / 12,
-  // 300 x 24 23 / 42, 300 x 100 68 / 200).
-  // (The grid counts fewer than 2^32 threads: inputs of 2^27 token-heads, 69 GB
-  // and more, take the 32-token tiles whatever their lengths.)
-  const bool chunks = !p.ctx_lens && ((p.total_tokens > 256 && p.total_tokens / 16 >= p.ns) ||
-                                      (int64_t)p.total_tokens * p.hkv >= (1 << 27));
-  const int tok = chunks ? kRun : 8;
-  const int64_t tiles = ((int64_t)p.total_tokens + tok - 1) / tok;
-  const dim3 grid((unsigned)(tiles * p.hkv));
-  return chunks ? launch_kernel(kv_append_kernel<kRun>, grid, dim3(kThreads), stream, p)
-                : launch_kernel(kv_append_kernel<8>, grid, dim3(kThreads), stream, p);
+  const int tile = append_tile(p.ctx_lens != nullptr, p.ns, p.total_tokens, p.hkv);
+  const dim3 grid((unsigned)append_groups(tile, p.total_tokens, p.hkv));
+  const auto kernel = tile == 8 ? kv_append_kernel<8> : tile == 16 ? kv_append_kernel<16> : kv_append_kernel<32>;
+  return launch_kernel(kernel, grid, dim3(kThreads), stream, p);
 }
 
 }  // namespace hswa
