@@ -26,9 +26,11 @@ namespace hswa {
 //   8 x 1536, aligned                        20.5 / 21.5 / 16.6
 //   8 x 1500, unaligned                      58.1 / 18.9 / 18.1
 //   2048 aligned among 256 single ones       10.7 / 11.4 / 11.9
-// (A grid holds fewer than 2^32 threads: inputs of 2^27 token-heads, 69 GB and
-// more, take 32-token tiles whatever their lengths.)
+// A grid holds fewer than 2^32 threads, counted in whole tiles: calls that
+// smaller tiles would take past that (from just under 2^27 token-heads on,
+// 69 GB of input) take 32-token ones whatever their lengths.
 constexpr int kAppendThreads = 256;
+constexpr int64_t kAppendMaxGroups = (int64_t{1} << 32) / kAppendThreads - 1;
 
 constexpr int64_t append_groups(int tile, int32_t total_tokens, int32_t hkv) {
   return ((int64_t)total_tokens + tile - 1) / tile * hkv;
@@ -37,8 +39,8 @@ constexpr int64_t append_groups(int tile, int32_t total_tokens, int32_t hkv) {
 constexpr int append_tile(bool single, int32_t ns, int32_t total_tokens, int32_t hkv) {
   const bool runs = !single && ((total_tokens > 512 && total_tokens / 16 >= ns) ||
                                 (total_tokens > 256 && total_tokens / 64 >= ns));
-  if ((int64_t)total_tokens * hkv >= (1 << 27)) return 32;
-  return !runs ? 8 : total_tokens / 40 < ns ? 16 : 32;
+  const int tile = !runs ? 8 : total_tokens / 40 < ns ? 16 : 32;
+  return append_groups(tile, total_tokens, hkv) <= kAppendMaxGroups ? tile : 32;
 }
 
 }  // namespace hswa

@@ -4,6 +4,8 @@
   stack under the address and undefined-behaviour sanitizers: counting,
   matching, evicting a deep subtree and teardown work level by level without
   recursion (tests/native/prefix_tree_deep.cpp).
+* The tile of a kv_append launch at the edges of its rules, the size of a grid
+  among them (tests/native/append_tile.cpp).
 * The host code of libhswa (the C ABI's argument validation, the allocator,
   the prefix tree) built with the same sanitizers and run under the CPU tests
   that drive it through the C ABI: test_allocator.py, test_prefix_tree.py and
@@ -35,6 +37,14 @@ def test_prefix_tree_deep_path(tmp_path):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1")
     r = subprocess.run([exe, "200000"], preexec_fn=_small_stack, capture_output=True, text=True, env=env, timeout=300)
     assert r.returncode == 0 and r.stdout.startswith("ok 200000"), r.stdout + r.stderr[-3000:]
+
+
+def test_append_grid_edges(tmp_path):
+    exe = str(tmp_path / "append_tile")
+    build_lib._run([build_lib.CXX, "-std=c++17", *build_lib.SAN_FLAGS, "-I", build_lib.CSRC,
+                    os.path.join(ROOT, "tests", "native", "append_tile.cpp"), "-o", exe])
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr[-3000:]
 
 
 def test_host_code_under_sanitizers(tmp_path):
