@@ -55,14 +55,14 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 # measured again.
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
-                            "sha256": "6ffdde6260ad42115a25fb27f49316b6e38d2c7b59e7ef547d3f414bdaa6b178",
-                            "fetch_bytes": 8609247198, "write_bytes": 5574727},
+                            "sha256": "cdcc305f60ae71c94206e8c0d2564ac45a53f925a071106fd327cd0aad5e8f2b",
+                            "fetch_bytes": 8609264647, "write_bytes": 5574745},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
-                     "sha256": "ba494e313af1e8dabd10fb160a420f29f4bc5c65788a36993632c3da1378c557",
-                     "fetch_bytes": 453294531, "write_bytes": 141434798},
+                     "sha256": "052d7f427303f17bf18e6bacd431e69d3fefee04e093a3b9a1d8c2fd8f175dc6",
+                     "fetch_bytes": 453172322, "write_bytes": 141393401},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
-                    "sha256": "2fc7264bd8e57f0207fa50361d0686b7aab043e00ee01a746e1cf1f1f838dda9",
-                    "fetch_bytes": 184855306, "write_bytes": 147648860},
+                    "sha256": "d173b36396310cb48859492145807887f499ddfbe6dda8bf7370ffd648c95153",
+                    "fetch_bytes": 184856219, "write_bytes": 147176827},
 }
 
 

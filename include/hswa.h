@@ -209,11 +209,18 @@ hswa_status hswa_prefill(hswa_layer layer, const hswa_shape *shape, const hswa_c
  * chunk over a long prefix, a few ragged chunks) does not fill the device with
  * one workgroup per tile; given a workspace, the key ranges of all tiles are
  * cut into equal spans, one per compute unit, and the fp32 partials of a tile
- * met by several spans are merged by the log-sum-exp identity.
+ * met by several spans are merged by the log-sum-exp identity. The kernel
+ * decides from cu_seqlens and prefix_lens whether the cut gains, whatever the
+ * width of the block table; a call that is not cut gives the same bits as
+ * hswa_prefill, a cut one the same values up to rounding.
  * hswa_prefill_workspace_bytes: the bytes such a call takes (about 65 MiB,
- * whatever its size), 0 for calls that do not gain from the split. A NULL
- * workspace, or one given to a call that needs none, is hswa_prefill; one too
- * small for a call that needs it is HSWA_ERR_CAPACITY. workspace: device,
+ * whatever its size), 0 for calls that cannot gain with any context that the
+ * table (cache->table_stride pages a sequence) holds. A call that is found not
+ * to gain takes a few microseconds more than hswa_prefill; a caller that knows
+ * a closer bound on the contexts hands this query a cache with table_stride set
+ * to the pages of that bound, and uses hswa_prefill where it returns 0.
+ * A NULL workspace, or one given to a call that needs none, is hswa_prefill; one
+ * too small for a call that needs it is HSWA_ERR_CAPACITY. workspace: device,
  * 16-byte aligned, free for other use once the call's work has completed. */
 size_t hswa_prefill_workspace_bytes(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache,
                                     int32_t ns, int32_t total_tokens, int32_t max_chunk_len);

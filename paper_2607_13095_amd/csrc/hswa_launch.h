@@ -96,8 +96,8 @@ hipError_t launch_decode(const DecodeParams &p, hipStream_t stream);
 bool decode_append_fused(const DecodeParams &p);
 hipError_t launch_decode_append(const DecodeParams &p, hipStream_t stream);
 hipError_t launch_prefill(const PrefillParams &p, hipStream_t stream);
-// FULL prefill cut into equal spans of key tiles (prefill.hip): whether a call
-// gains from it, the workspace it takes (any call), the launch.
+// FULL prefill that may be cut into equal spans of key tiles (prefill.hip):
+// whether a call can gain from it, the workspace it takes (any call), the launch.
 bool prefill_split_fits(const PrefillParams &p);
 size_t prefill_split_bytes();
 hipError_t launch_prefill_split(const PrefillParams &p, void *workspace, hipStream_t stream);

@@ -31,7 +31,10 @@
 // A call with few tiles (or few in its last round) leaves compute units idle:
 // given a workspace, its key tiles are cut into equal spans instead, one per
 // workgroup, and prefill_merge_kernel combines the pieces of a tile (295 tokens
-// over 22.5K cached, 80 tiles: 498 -> 209 us). A span walks its tiles in a loop
+// over 22.5K cached, 80 tiles: 498 -> 209 us). Whether that gains depends on the
+// lengths, which only the device has: the host rules calls out by what the block
+// table can hold, and the kernel decides (split_gains); where it does not gain
+// the kernel works as the unsplit one. A span walks its tiles in a loop
 // around the same code; what the tile loop does not need is kept out of its
 // registers (walk state in LDS, parameters and lane addresses formed anew per
 // tile), which a plain loop spilled at +5% per key tile.
@@ -57,8 +60,8 @@ static_assert((kBufs & (kBufs - 1)) == 0, "buffer indices are taken modulo kBufs
 constexpr float kLaneSumLimit = 4096.f;
 constexpr int kSplitSpans = 256;  // spans of the split order: one workgroup per CU
 constexpr int kTileCost = 5;      // what a query tile costs besides its key tiles, in key tiles
-constexpr int kWholeSlack = 6;    // what the partials and their merge cost
-constexpr double kSplitGain = 14;  // key tiles a split has to gain (its partials, their merge, its own order)
+constexpr int kSplitGain = 14;    // key tiles a split has to gain (its partials, their merge, its own order)
+constexpr int kCutCost = 13;      // the same once its kernels are launched
 constexpr int kMinSpan = 8;       // least worth of a span
 // LDS operand reads in flight ahead of the matrix products (8: +0.6%, 10: +1.6%,
 // 6: +0.3% on 4 x 2048 over 8192)
@@ -128,94 +131,125 @@ __device__ __forceinline__ int key_tiles(int t, int npos, int c, int pre, int w)
 struct Walk {
   int64_t one;    // worth of the query tiles of one KV head
   int64_t per;    // worth of a span
-  int64_t u, u1;  // this span's rest [u, u1)
+  int64_t u0;     // this span's start
+  int64_t u, u1;  // its rest [u, u1)
   int64_t next;   // where the query tile at u ends (u1 if the span ends in it)
-  bool whole;     // every workgroup takes one whole tile, worth 1
 };
+
+// Inclusive scan over the wave's lanes with `op` (`none`: its identity) by data
+// movement inside the vector ALU; lane 63 ends up with the result of all lanes.
+template <int kCtrl, int kRows, typename T>
+__device__ __forceinline__ T lane_move(T none, T x) {
+  if constexpr (sizeof(T) == 8) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x), o = __builtin_bit_cast(uint64_t, none);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)o, (int)u, kCtrl, kRows, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(o >> 32), (int)(u >> 32), kCtrl, kRows, 0xf, false);
+    return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+  } else {
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, none), __builtin_bit_cast(int, x),
+                                                             kCtrl, kRows, 0xf, false));
+  }
+}
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_scan(T x, T none, Op op) {
+  x = op(x, lane_move<0x111, 0xf>(none, x));  // from 1, 2, 4, 8 lanes down in a row of 16
+  x = op(x, lane_move<0x112, 0xf>(none, x));
+  x = op(x, lane_move<0x114, 0xf>(none, x));
+  x = op(x, lane_move<0x118, 0xf>(none, x));
+  x = op(x, lane_move<0x142, 0xa>(none, x));  // a row's last lane to the next row (rows 1 and 3)
+  x = op(x, lane_move<0x143, 0xc>(none, x));  // lane 31 to the upper rows
+  return x;
+}
+__device__ __forceinline__ float last_lane(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), kWave - 1));
+}
+
+// Whether cutting the call into spans gains, by its lengths (lane b holds
+// sequence b; every wave finds it by itself). In key tiles, a query tile worth
+// its key tiles plus kTileCost, the unsplit call takes the largest of: the load
+// of the fullest XCD (sequences taken as alike); its rounds of the shortest
+// tiles; and, for a sequence whose last (sequence, KV head) pair comes after
+// others on its XCD, the time until a compute unit is free for it and then its
+// longest tile. Each round also takes this decision anew (about 1.3 us, a
+// unit), and the merge is launched either way. The split one takes the average
+// over all compute units and kCutCost. us per call unsplit by hswa_prefill / whole
+// tiles here / cut, with the gain by this rule and the 13 it is held against (the
+// block table 128K positions wide, 64 / 8 heads, except where other heads are given):
+//   300 tokens over none             16.9 / 20.2 / -       3
+//   600 over none                    24.5 / 28.2 / 34.5    8
+//   1500 over none                   48.0 / 52.5 / 66.3    5
+//   4 x 600 over none                47.2 / 52.8 / 60.3    6
+//   8 x 64 over 1000                 34.4 / 38.4 / 40.0   12
+//   1000 over none, 16 / 16          35.9 / 40.0 / 36.6   14
+//   20 - 780 over 100, 20 of them,
+//     PG 16, 32 / 8                 106.7 / 116.6 / 107.7  13.5
+//   64 over 1000                     32.6 /  -   / 30.6   15
+//   446 - 1471 over 463 - 2957,
+//     4 of them, PG 16, 32 / 8      139   /  -   / 119    33
+//   600 over 4000                   111   /  -   / 95.7   35
+//   295 over 22.5K                  494   /  -   / 212   250
+// A table as wide as the context is long takes the same decisions. (By table
+// width alone 600 and 1500 tokens over none were cut: 34.5 and 66.3 us.)
+__device__ __forceinline__ bool split_gains(const PrefillParams &p, int npos, int lane) {
+  constexpr float kXcdCus = kSplitSpans / kXcds;
+  const auto add = [](float a, float b) { return a + b; };
+  const auto most = [](float a, float b) { return fmaxf(a, b); };
+  const auto least = [](float a, float b) { return fminf(a, b); };
+  const float heads = (float)p.hkv * (1.f / kXcds), others = fmaxf(heads - 1.f, 0.f);  // pairs of a sequence on an XCD
+  float count = 0.f, sum = 0.f, late = 0.f, shortest = FLT_MAX;
+  for (int b0 = 0; b0 < p.ns; b0 += kWave) {
+    const int b = b0 + lane;
+    const int c = b < p.ns ? chunk_len(p, b) : 0;
+    float n = 0.f, s = 0.f, first = 0.f, longest = 0.f;  // query tiles, their worth, the first's and the last's
+    if (c > 0) {
+      const int pre = p.prefix_lens[b];
+      const int cached = kTileCost + (pre > 0 ? ((pre - 1) >> 6) + 1 : 0);
+      n = (float)((c + npos - 1) >> __builtin_ctz(npos));  // (npos is a power of two)
+      first = (float)(cached + ((min(npos, c) - 1) >> 6) + 1);
+      longest = (float)(cached + ((c - 1) >> 6) + 1);
+      s = n * .5f * (first + longest);
+    }
+    const float cn = wave_scan(n, 0.f, add), cs = wave_scan(s, 0.f, add);
+    const float bn = heads * (count + cn - n) + others * n, bs = heads * (sum + cs - s) + others * s;  // before the last pair
+    if (c > 0) {
+      late = fmaxf(late, longest + (bn >= kXcdCus ? bs * (1.f / kXcdCus - .5f * __builtin_amdgcn_rcpf(bn)) : 0.f));
+      shortest = fminf(shortest, first);
+    }
+    count += last_lane(cn);
+    sum += last_lane(cs);
+  }
+  late = last_lane(wave_scan(late, 0.f, most));
+  shortest = last_lane(wave_scan(shortest, FLT_MAX, least));
+  const float share = (float)((p.ns * p.hkv + kXcds - 1) / kXcds) * __builtin_amdgcn_rcpf((float)p.ns * kXcdCus);
+  const float unsplit = fmaxf(late, fmaxf(sum * share, ceilf(count * share) * shortest));
+  const float rounds = ceilf(count * (float)p.hkv * (1.f / kSplitSpans));
+  const float spans = fmaxf((float)kMinSpan, sum * (float)p.hkv * (1.f / kSplitSpans));
+  return __builtin_amdgcn_readfirstlane((int)(count > 0.f && unsplit + rounds - spans >= (float)kCutCost)) != 0;
+}
 
 typedef __attribute__((address_space(4))) const PrefillParams KernArgs;
 
-// kCG: 16-column MFMA groups per wave, 128 kCG query rows per workgroup.
-// kPage: keys of a page, 64 standing for 64 and more.
-// kSplit: the work is cut into equal spans of key tiles, one per workgroup.
-template <int kCG, int kPage, bool kSplit>
-__global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
-  constexpr int kRows = 8 * 16 * kCG;
-  // kBufs tile buffers, each a K tile then a V^T tile (byte offsets below)
-  __shared__ __attribute__((aligned(16))) unsigned char s_lds[kBufs * kBufBytes];
-  // split: key tiles up to and including each (sequence, query tile) of one KV
-  // head, their sum and its per-wave parts, the current query tile
-  __shared__ int64_t s_cum[kSplit ? kThreads : 1], s_wave[kSplit ? kThreads / kWave : 1];
-  __shared__ Walk s_walk;
-  __shared__ int s_tile[3];
+// LDS of a workgroup: kBufs tile buffers, each a K tile then a V^T tile (byte
+// offsets below).
+struct __attribute__((aligned(16))) TileBufs {
+  unsigned char b[kBufs * kBufBytes];
+};
+// And of a span: key tiles up to and including each (sequence, query tile) of
+// one KV head, their per-wave parts, the walk, the current query tile.
+struct SpanLds {
+  int64_t cum[kThreads], wave[kThreads / kWave];
+  Walk walk;
+  int tile[3];
+};
 
-  int b, g, tq;
-  [[maybe_unused]] const int span = (int)(blockIdx.x % kXcds) * (kSplitSpans / kXcds) + (int)(blockIdx.x / kXcds);
-  if constexpr (kSplit) {
-    const PrefillParams &p = p0;
-    const int npos = kRows / p.group, ntq = (p.max_chunk_len + npos - 1) / npos;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    // Split order: the query tiles of every KV head, sequence and position, in
-    // that order, each worth its key tiles plus kTileCost, are cut into equal
-    // spans of `per`, one span per workgroup (workgroup ids go to the XCDs
-    // round-robin, so an XCD gets consecutive spans: with 8 KV heads, one
-    // head). A query tile met by several spans gets a partial result from each,
-    // merged by prefill_merge_kernel.
-    // Where no tile is longer than a span by kWholeSlack and there is a
-    // workgroup for each, every workgroup takes one whole tile instead.
-    const int idx = tid;  // (sequence, query tile) pairs: at most one per thread (checked on the host)
-    const int bb = idx / ntq;
-    int64_t n = bb < p.ns ? key_tiles(idx - bb * ntq, npos, chunk_len(p, bb), p.prefix_lens[bb], p.pool.window) : 0;
-    n += n > 0 ? kTileCost : 0;
-    const auto scan = [&](int64_t v, int64_t &sum) {  // over the workgroup; sum: of all
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const int64_t o = __shfl_up(v, off, kWave);
-        if (lane >= off) v += o;
-      }
-      __syncthreads();
-      if (lane == kWave - 1) s_wave[wave] = v;
-      __syncthreads();
-      sum = 0;
-#pragma unroll
-      for (int w = 0; w < kThreads / kWave; ++w) {
-        if (w == wave) v += sum;
-        sum += s_wave[w];
-      }
-      return v;
-    };
-    int64_t one, per = 1;
-    int64_t cum = scan(n, one);
-    const int64_t cut = max((int64_t)kMinSpan, (one * p.hkv + kSplitSpans - 1) / kSplitSpans);
-    const bool long_tile = __syncthreads_or(n > cut + kWholeSlack) != 0;
-    const bool whole = (int64_t)__syncthreads_count(n > 0) * p.hkv <= kSplitSpans && !long_tile;
-    if (whole) cum = scan(n > 0 ? 1 : 0, one);
-    else per = cut;
-    s_cum[tid] = cum;
-    const int64_t total = one * p.hkv, u = span * per;
-    if (tid == 0) s_walk = Walk{one, per, u, min(total, u + per), 0, whole};
-    if (u >= total) {
-      if (tid == 0) p.ws_desc[span].pieces = 0;
-      return;
-    }
-  } else {
-    // XCD-aware order. Workgroup ids are dealt to the XCDs round-robin; the
-    // (sequence, KV head) pairs are dealt the same way, pair x + 8k to XCD x, so
-    // every query tile of a pair runs on one XCD and shares its K/V in that L2,
-    // while pairs of unequal length (different prefixes) spread over all XCDs.
-    // Within a pair the longest query tiles (the last ones) go first.
-    const PrefillParams &p = p0;
-    const int npos = kRows / p.group, ntq = (p.max_chunk_len + npos - 1) / npos;
-    const int npairs = p.ns * p.hkv;
-    const int xcd = (int)(blockIdx.x % kXcds);
-    const int local = (int)(blockIdx.x / kXcds);
-    const int k = local / ntq;
-    tq = ntq - 1 - (local - k * ntq);
-    const int pair = xcd + kXcds * k;
-    if (pair >= npairs) return;
-    b = pair / p.hkv;
-    g = pair - b * p.hkv;
-  }
+// One query tile (tq of sequence b, KV head g), or with kSplit the query tiles
+// of a span. kCG: 16-column MFMA groups per wave, 128 kCG query rows per
+// workgroup. kPage: keys of a page, 64 standing for 64 and more.
+template <int kCG, int kPage, bool kSplit>
+__device__ __forceinline__ void prefill_tiles(const PrefillParams &p0, TileBufs &bufs, [[maybe_unused]] SpanLds *sl,
+                                              [[maybe_unused]] int span, int b, int g, int tq) {
+  constexpr int kRows = 8 * 16 * kCG;
+  unsigned char *const s_lds = bufs.b;
   for (;;) {
   int tid = threadIdx.x;
   // opaque, so that the lane addresses below are formed anew for each query
@@ -239,29 +273,29 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
   const int shift = pv.pg_shift, pg = 1 << shift;
   const float c2 = p.scale_log2;
 
-  int j0 = 0, j1 = 0;  // split: key tiles [j0, j1) of the query tile
+  int j0 = 0, j1 = INT_MAX;  // key tiles [j0, j1) of the query tile
   if constexpr (kSplit) {
     // the query tile that holds unit u
     __syncthreads();
-    const int64_t gl = s_walk.u / s_walk.one;
-    const int64_t rem = s_walk.u - gl * s_walk.one;
-    const int64_t lo = tid > 0 ? s_cum[tid - 1] : 0, hi = s_cum[tid];
+    const int64_t gl = sl->walk.u / sl->walk.one;
+    const int64_t rem = sl->walk.u - gl * sl->walk.one;
+    const int64_t lo = tid > 0 ? sl->cum[tid - 1] : 0, hi = sl->cum[tid];
     if (lo <= rem && rem < hi) {
-      s_tile[0] = tid;
-      const int64_t left = min(hi - rem, s_walk.u1 - s_walk.u);
-      s_tile[1] = (int)max((int64_t)0, rem - lo - kTileCost);
-      s_tile[2] = s_walk.whole ? INT_MAX : (int)(rem + left - lo - kTileCost);
-      s_walk.next = s_walk.u + left;
+      sl->tile[0] = tid;
+      const int64_t left = min(hi - rem, sl->walk.u1 - sl->walk.u);
+      sl->tile[1] = (int)max((int64_t)0, rem - lo - kTileCost);
+      sl->tile[2] = (int)(rem + left - lo - kTileCost);
+      sl->walk.next = sl->walk.u + left;
     }
     __syncthreads();
     g = __builtin_amdgcn_readfirstlane((int)gl);
-    const int tile = __builtin_amdgcn_readfirstlane(s_tile[0]);
+    const int tile = __builtin_amdgcn_readfirstlane(sl->tile[0]);
     b = tile / ntq;
     tq = tile - b * ntq;
-    j0 = __builtin_amdgcn_readfirstlane(s_tile[1]);
-    j1 = __builtin_amdgcn_readfirstlane(s_tile[2]);
+    j0 = __builtin_amdgcn_readfirstlane(sl->tile[1]);
+    j1 = __builtin_amdgcn_readfirstlane(sl->tile[2]);
     if (j1 <= 0) {  // the span ends before the tile's first key tile
-      if (tid == 0 && s_walk.u == span * s_walk.per) p.ws_desc[span].pieces = 0;
+      if (tid == 0 && sl->walk.u == sl->walk.u0) p.ws_desc[span].pieces = 0;
       return;
     }
   }
@@ -270,7 +304,6 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
   const int C = chunk_len(p, b);
   const int P = p.prefix_lens[b];
   const int q0 = tq * npos;
-  if (!kSplit && q0 >= C) return;
   const int q1 = min(C, q0 + npos) - 1;
   const int pfirst = P + q0, plast = P + q1;
   const int W = pv.window;
@@ -783,9 +816,9 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
   // ---- normalise and write ----
   bool last = !kSplit;
   if constexpr (kSplit) {
-    const int64_t u = s_walk.u, per = s_walk.per;
+    const int64_t u = sl->walk.u, per = sl->walk.per;
     const bool whole = ntiles == nall;
-    if (tid == 0 && u == span * per) {
+    if (tid == 0 && u == sl->walk.u0) {
       // the span's first query tile, for the merge: it takes up a tile at the
       // second of its spans
       const int64_t k0 = u - j0, first = k0 / per;  // k0: the place of the tile's first key tile, if j0 > 0
@@ -812,10 +845,10 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
         if (q == 0) p.ws_lse[(base + cg) * 16 + r] = m[cg] + __log2f(l);
       }
     }
-    const int64_t unext = s_walk.next;
-    const bool done = unext >= s_walk.u1;
-    __syncthreads();  // every wave has read s_walk and the tile buffers
-    if (tid == 0) s_walk.u = unext;
+    const int64_t unext = sl->walk.next;
+    const bool done = unext >= sl->walk.u1;
+    __syncthreads();  // every wave has read sl->walk and the tile buffers
+    if (tid == 0) sl->walk.u = unext;
     if (!whole) {
       if (done) return;
       continue;
@@ -838,6 +871,81 @@ __global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p0) {
     store_out_row(orow, w, q, cval[cg]);
   }
   if (last) break;
+  }
+}
+
+// kSplit: a call that may be cut into equal spans of key tiles, one per
+// workgroup.
+template <int kCG, int kPage, bool kSplit>
+__global__ __launch_bounds__(kThreads) void prefill_kernel(PrefillParams p) {
+  constexpr int kRows = 8 * 16 * kCG;
+  __shared__ TileBufs bufs;
+  const int npos = kRows / p.group, ntq = (p.max_chunk_len + npos - 1) / npos;
+  // XCD-aware order of whole query tiles. Workgroup ids are dealt to the XCDs
+  // round-robin; the (sequence, KV head) pairs are dealt the same way, pair
+  // x + 8k to XCD x, so every query tile of a pair runs on one XCD and shares
+  // its K/V in that L2, while pairs of unequal length (different prefixes)
+  // spread over all XCDs. Within a pair the longest query tiles (the last ones)
+  // go first. False: no tile for this workgroup.
+  int b = 0, g = 0, tq = 0;
+  auto take_whole = [&]() {
+    const int npairs = p.ns * p.hkv;
+    const int xcd = (int)(blockIdx.x % kXcds);
+    const int local = (int)(blockIdx.x / kXcds);
+    const int k = local / ntq;
+    tq = ntq - 1 - (local - k * ntq);
+    const int pair = xcd + kXcds * k;
+    if (pair >= npairs) return false;
+    b = pair / p.hkv;
+    g = pair - b * p.hkv;
+    return tq * npos < chunk_len(p, b);
+  };
+  if constexpr (kSplit) {
+    __shared__ SpanLds sl;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const bool extra = blockIdx.x >= kSplitSpans;  // whole tiles only
+    if (extra && !take_whole()) return;
+    if (!split_gains(p, npos, lane)) {
+      // No gain: a whole query tile each, as in the unsplit call, and nothing to
+      // merge. (The same code as there: deciding inside the walk of the spans
+      // took both of them 2% more.)
+      if (tid == 0 && !extra) p.ws_desc[blockIdx.x].pieces = 0;
+      if (extra || take_whole()) prefill_tiles<kCG, kPage, false>(p, bufs, nullptr, 0, b, g, tq);
+      return;
+    }
+    if (extra) return;
+    // Split order: the query tiles of every KV head, sequence and position, in
+    // that order, each worth its key tiles plus kTileCost, are cut into equal
+    // spans of `per`, one span per workgroup (workgroup ids go to the XCDs
+    // round-robin, so an XCD gets consecutive spans: with 8 KV heads, one
+    // head). A query tile met by several spans gets a partial result from
+    // each, merged by prefill_merge_kernel.
+    const int span = (int)(blockIdx.x % kXcds) * (kSplitSpans / kXcds) + (int)(blockIdx.x / kXcds);
+    const int idx = tid;  // (sequence, query tile) pairs: at most one per thread (checked on the host)
+    const int bb = idx / ntq;
+    int64_t n = bb < p.ns ? key_tiles(idx - bb * ntq, npos, chunk_len(p, bb), p.prefix_lens[bb], p.pool.window) : 0;
+    n += n > 0 ? kTileCost : 0;
+    n = wave_scan(n, (int64_t)0, [](int64_t x, int64_t y) { return x + y; });
+    if (lane == kWave - 1) sl.wave[wave] = n;
+    __syncthreads();
+    int64_t one = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w) {
+      if (w == wave) n += one;
+      one += sl.wave[w];
+    }
+    sl.cum[tid] = n;
+    const int64_t total = one * p.hkv, per = max((int64_t)kMinSpan, (total + kSplitSpans - 1) / kSplitSpans);
+    const int64_t u = span * per;
+    if (tid == 0) sl.walk = Walk{one, per, u, u, min(total, u + per), 0};
+    if (u >= total) {
+      if (tid == 0) p.ws_desc[span].pieces = 0;
+      return;
+    }
+    prefill_tiles<kCG, kPage, true>(p, bufs, &sl, span, 0, 0, 0);
+  } else {
+    if (!take_whole()) return;
+    prefill_tiles<kCG, kPage, false>(p, bufs, nullptr, 0, b, g, tq);
   }
 }
 
@@ -893,16 +1001,17 @@ hipError_t launch_prefill_rows(const PrefillParams &p, dim3 grid, hipStream_t st
   }
 }
 
-// Whether a FULL call is cut into spans of key tiles. The host knows the chunk
-// lengths only by their largest and their sum, and the prefix lengths only as
-// what the block table can hold; in key tiles it takes the unsplit call as the
-// largest of its longest tile, its rounds of the shortest tiles and its average
-// load on the fullest XCD, and the split one as the average over all compute
-// units. The line of kSplitGain is where both measured the same: with 64 / 8
-// heads, 64 tokens over 1000 cached (gain 14) 32 us unsplit and 29 split, 8 x
-// 64 over 1000 (11) 37 and 41, 1500 over none (3) 48 and 66, 4 x 2048 over
-// 8192 (0) 1915 and 2150, 4 ragged chunks at PG 16 (60) 138 and 115, 295 over
-// 22.5K (246) 498 and 209, 32 over 32768 (480) 698 and 54.
+// Whether a FULL call can gain from a cut into spans of key tiles. The host knows
+// the chunk lengths only by their largest and their sum, and the prefix lengths
+// only as what the block table can hold; in key tiles it takes the unsplit call
+// as the largest of its longest tile, its rounds of the shortest tiles and its
+// average load on the fullest XCD, and the split one as the average over all
+// compute units. Calls that fill the device whatever their contexts stay
+// unsplit here (4 x 2048 over 8192, gain 0: 1915 us, cut 2150); for the others the
+// kernel decides by the lengths themselves (split_gains), which costs a call that
+// is then not cut 3 to 5 us. With a context as long as the table, the line of
+// kSplitGain is where both measured the same: with 64 / 8 heads, 64 tokens over
+// 1000 (14) 32 us unsplit and 30 split, 8 x 64 over 1000 (11) 34 and 40.
 bool prefill_split_fits(const PrefillParams &p) {
   if (p.pool.window > 0 || p.ns <= 0 || p.max_chunk_len <= 0 || p.total_tokens <= 0) return false;
   const int npos = 128 * kRowGroups / p.group;
@@ -930,7 +1039,12 @@ hipError_t launch_prefill_split(const PrefillParams &p0, void *workspace, hipStr
   p.ws_o = reinterpret_cast<float *>(ws);
   p.ws_lse = reinterpret_cast<float *>(ws + kSplitOBytes);
   p.ws_desc = reinterpret_cast<PrefillDesc *>(ws + kSplitOBytes + kSplitLseBytes);
-  const hipError_t e = launch_prefill_rows<true>(p, dim3(kSplitSpans), stream);
+  // a workgroup per span, and one per query tile should the lengths show no gain
+  const int npos = 128 * kRowGroups / p.group;
+  const int64_t ntq = (p.max_chunk_len + npos - 1) / npos;
+  const int64_t pairs_per_xcd = ((int64_t)p.ns * p.hkv + kXcds - 1) / kXcds;
+  const int64_t grid = std::max<int64_t>(kSplitSpans, pairs_per_xcd * ntq * kXcds);
+  const hipError_t e = launch_prefill_rows<true>(p, dim3((unsigned)grid), stream);
   if (e != hipSuccess) return e;
   return launch_kernel(prefill_merge_kernel<kRowGroups>, dim3((kSplitSpans - 1) * 8 * kRowGroups), dim3(4 * kWave),
                        stream, p);

@@ -381,10 +381,17 @@ def _in_private_pool(t) -> bool:
 
 
 def prefill(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, cu_seqlens, prefix_lens,
-            max_chunk_len: int, out, stream=None):
+            max_chunk_len: int, out, stream=None, max_context=None):
     """Chunked prefill; q, out [T, Hq, D], k_new / v_new [T, Hkv, D]; see
-    hswa_prefill and, for FULL calls with few query tiles, hswa_prefill_ws
-    (their scratch is held for the length of the call only)."""
+    hswa_prefill and, for FULL calls with few query tiles, hswa_prefill_ws, whose
+    scratch (about 65 MiB) this call takes from torch's caching allocator and
+    gives back when it returns. Without scratch (a stream that is not torch's, a
+    capture that torch did not begin, no memory left) the call runs unsplit:
+    slower where a short chunk follows a long prefix, and rounded differently.
+    max_context: a bound on every sequence's prefix + chunk, if the host knows
+    one (default: what the block table holds). It decides only whether scratch is
+    taken: a call that cannot gain within it saves the few microseconds in which
+    the kernel finds that out from the lengths."""
     _torch()
     ns = cu_seqlens.numel() - 1
     t = int(q.shape[0])
@@ -396,7 +403,11 @@ def prefill(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, cu_seqlen
     _check_cache(shape, cache, ns)
     sh, ca = shape.c(), cache.c()
     lib, lc, sp, cp, mc = load(), layer.c(), shape.ref(), cache.ref(), int(max_chunk_len)
-    need = lib.hswa_prefill_workspace_bytes(lc, sp, cp, ns, t, mc)
+    qp = cp
+    if max_context is not None:  # the query takes the table for no wider than the bound
+        pages = max(1, -(-int(max_context) // shape.page_size))
+        qp = ctypes.byref(_Cache(ca.k_pool, ca.v_pool, ca.num_pages, ca.block_table, min(ca.table_stride, pages)))
+    need = lib.hswa_prefill_workspace_bytes(lc, sp, qp, ns, t, mc)
     ws = _prefill_scratch(need, stream) if need else None
     if ws is None:
         st = lib.hswa_prefill(lc, sp, cp, *args, ns, t, mc, o, _stream(stream))

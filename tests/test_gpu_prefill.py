@@ -10,6 +10,7 @@ import torch
 import synth
 from oracle import attention as OA
 from paper_2607_13095_amd import hswa
+from paper_2607_13095_amd.kvcache import LayerKV, pages_for
 from tests.hswa_testlib import (SeqHistory, append_history, assert_close, i32, make_layer, to_dev, to_f64)
 
 pytestmark = pytest.mark.gpu
@@ -229,6 +230,77 @@ def test_prefill_split_table_larger_than_context(gpu_lib, prefix, chunk):
     ref = OA.prefill(OA.bf16_bits_to_f64(qb), OA.bf16_bits_to_f64(hist.k[0]), OA.bf16_bits_to_f64(hist.v[0]), prefix,
                      None)
     assert_close(to_f64(out), ref, f"{chunk} over {prefix}")
+
+
+def _split_and_unsplit(hq, hkv, pg, prefixes, chunks, width):
+    """hswa_prefill_ws (through the binding) and hswa_prefill on a block table of
+    `width` positions a sequence, with random pools."""
+    shape, layer = hswa.Shape(hq, hkv, 128, pg), hswa.Layer.full()
+    final = [a + b for a, b in zip(prefixes, chunks)]
+    kv = LayerKV(layer, shape, final, perm=np.random.default_rng(3).permutation(pages_for(layer, pg, final)), fill=0.0,
+                 stride=max(width // pg, max(-(-n // pg) for n in final)))
+    g = torch.Generator(device="cuda").manual_seed(9)
+    for pool in (kv.k_pool, kv.v_pool):
+        pool.normal_(generator=g)
+    t, ns = sum(chunks), len(chunks)
+    q, k, v = (torch.randn((t, h, 128), generator=g, device="cuda").to(torch.bfloat16) for h in (hq, hkv, hkv))
+    cu, pre, mc = i32(synth.cu_seqlens(chunks)), i32(prefixes), max(chunks)
+    args = (layer.c(), shape.c(), kv.cache.c())
+    assert hswa.load().hswa_prefill_workspace_bytes(*args, ns, t, mc) > 0
+    cut, unsplit = (torch.full((t, hq, 128), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    hswa.prefill(layer, shape, kv.cache, q, k, v, cu, pre, mc, cut)
+    assert hswa.load().hswa_prefill(*args, q.data_ptr(), k.data_ptr(), v.data_ptr(), cu.data_ptr(), pre.data_ptr(), ns,
+                                    t, mc, unsplit.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    return cut, unsplit
+
+
+@pytest.mark.parametrize("hq,hkv,pg,prefixes,chunks,cuts", [
+    (64, 8, 64, [0], [300], False),
+    (64, 8, 64, [0], [1500], False),                       # more tiles than workgroups of the cut
+    (64, 8, 64, [1000] * 8, [64] * 8, False),
+    (64, 8, 16, [0] * 4, [600, 1, 0, 577], False),         # an empty sequence, part tiles
+    (24, 12, 32, [50] * 3, [300, 30, 600], False),         # heads that do not divide over the XCDs
+    (8, 1, 64, [0] * 70, [20] * 70, False),                # more sequences than lanes
+    (64, 8, 64, [64], [700], False),
+    (64, 8, 64, [4000], [600], True),
+    (16, 16, 64, [0], [1000], True),                       # few tiles, whatever the prefix
+    (48, 3, 64, [0, 300], [900, 2000], True),
+    (8, 1, 64, [0] * 69 + [6000], [20] * 70, True),        # one long context among many short ones
+    (32, 8, 16, [463, 750, 695, 2957], [446, 1471, 731, 615], True),
+])
+def test_prefill_cut_by_lengths(gpu_lib, hq, hkv, pg, prefixes, chunks, cuts):
+    """Whether a call is cut into spans follows from its lengths, not from the
+    width of its block table: one that does not gain works as the unsplit call,
+    bit for bit (no sum is taken in another order), one that gains is cut."""
+    print(f"[prefill-cut] {hq}/{hkv} PG={pg} {prefixes[-1]} {chunks[:4]} ns={len(chunks)}", flush=True)
+    for width in (32768, 131072):
+        cut, unsplit = _split_and_unsplit(hq, hkv, pg, prefixes, chunks, width)
+        assert not torch.isnan(unsplit).any()
+        assert torch.equal(cut, unsplit) != cuts, f"table of {width}"
+        assert_close(to_f64(cut), to_f64(unsplit), f"table of {width}")
+
+
+def test_prefill_max_context_takes_no_scratch(gpu_lib, monkeypatch):
+    """A call that cannot gain within max_context asks for no scratch; the bound
+    changes no value, also where it is too small."""
+    shape, layer = hswa.Shape(64, 8, 128, 64), hswa.Layer.full()
+    kv = LayerKV(layer, shape, [5000], fill=0.0, stride=2048)
+    kv.k_pool.normal_(), kv.v_pool.normal_()
+    taken = []
+    scratch = hswa._prefill_scratch
+    monkeypatch.setattr(hswa, "_prefill_scratch", lambda n, s: taken.append(n) or scratch(n, s))
+    for prefix, chunk, bounds in ((0, 1500, {None: 1, 1500: 0, 2048 * 64: 1, 10**12: 1}), (4000, 100, {None: 1, 4100: 1, 1: 0})):
+        q, k, v = (torch.randn((chunk, h, 128), device="cuda").to(torch.bfloat16) for h in (64, 8, 8))
+        outs = []
+        for bound, calls in bounds.items():
+            out = torch.full((chunk, 64, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+            taken.clear()
+            hswa.prefill(layer, shape, kv.cache, q, k, v, i32([0, chunk]), i32([prefix]), chunk, out, max_context=bound)
+            assert len(taken) == calls, (prefix, bound)
+            outs.append(to_f64(out))
+        for o in outs[1:]:
+            assert_close(o, outs[0], f"{chunk} over {prefix}")
 
 
 @pytest.mark.parametrize("pg", [16, 32, 64, 256])
