@@ -355,13 +355,13 @@ def kv_append(layer: Layer, shape: Shape, cache: Cache, k_new, v_new, cu_seqlens
 
 def _prefill_scratch(nbytes: int, stream):
     """Scratch for one call from torch's caching allocator, in the order of the
-    stream the call runs on, or None (the call then runs unsplit): on a raw
-    stream handle the allocator does not know, when the device is out of memory,
-    and under a stream capture that torch did not begin. (A graph captured by
-    torch owns the memory it allocates; in another capture the memory would be
-    handed out again while the graph still replays into it.)"""
+    stream the call runs on, or None (the call then runs unsplit): on a stream
+    that is not torch's, when the device is out of memory, and under a stream
+    capture that torch did not begin. (A graph captured by torch owns the memory
+    it allocates; in another capture the memory would be handed out again while
+    the graph still replays into it.)"""
     torch = _torch()
-    if isinstance(stream, int):
+    if stream is not None and not isinstance(stream, torch.cuda.Stream):
         return None
     with torch.cuda.stream(stream):
         try:
@@ -374,7 +374,7 @@ def _prefill_scratch(nbytes: int, stream):
 
 
 def _in_private_pool(t) -> bool:
-    """Whether the tensor's memory belongs to a graph's (or another private) pool."""
+    """Whether the memory belongs to a graph's (or another private) pool."""
     a = t.data_ptr()
     return any(s["address"] <= a < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
                for s in _torch().cuda.memory_snapshot())

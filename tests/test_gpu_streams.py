@@ -8,7 +8,13 @@ also appends its new keys, and the appends are idempotent (the same keys to
 the same slots), except that a chunk longer than the SWA ring's spare slots
 overwrites prefix keys; every step therefore first re-stores the prefill
 sequences' prefixes, so every run sees the same cache. The serial outputs are
-checked against the fp64 oracle on sampled rows as well."""
+checked against the fp64 oracle on sampled rows as well.
+
+A FULL prefill that takes scratch from torch takes it in the order of the stream
+it is given; on a stream that is not torch's, without memory, and in a capture
+that torch did not begin, it runs unsplit."""
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -17,6 +23,7 @@ import torch
 import synth
 from oracle import attention as OA
 from paper_2607_13095_amd import hswa
+from paper_2607_13095_amd.kvcache import LayerKV
 from tests.hswa_testlib import SeqHistory, append_history, assert_close, i32, make_layer, to_bits, to_dev, to_f64
 
 pytestmark = pytest.mark.gpu
@@ -110,3 +117,96 @@ def test_two_streams_match_serial(gpu_lib, kind, window):
     for rep, (op2, od2) in enumerate(outs):
         assert np.array_equal(to_bits(op2), ref_p), f"prefill rep {rep} differs from the serial run"
         assert np.array_equal(to_bits(od2), ref_d), f"decode rep {rep} differs from the serial run"
+
+
+class _ShortTurn:
+    """A FULL prefill that gains from being cut into spans: 40 tokens over 4000."""
+
+    def __init__(self):
+        self.shape, self.layer = hswa.Shape(16, 2, 128, 64), hswa.Layer.full()
+        self.kv = LayerKV(self.layer, self.shape, [4040], fill=0.0)
+        g = torch.Generator(device="cuda").manual_seed(4)
+        for pool in (self.kv.k_pool, self.kv.v_pool):
+            pool.normal_(generator=g)
+        self.q, self.k, self.v = (torch.randn((40, h, 128), generator=g, device="cuda").to(torch.bfloat16)
+                                  for h in (16, 2, 2))
+        self.cu, self.pre = i32([0, 40]), i32([4000])
+        self.out = torch.empty_like(self.q)
+        self.cut = self.run().clone()
+        lib = hswa.load()
+        assert lib.hswa_prefill(self.layer.c(), self.shape.c(), self.kv.cache.c(), self.q.data_ptr(), self.k.data_ptr(),
+                                self.v.data_ptr(), self.cu.data_ptr(), self.pre.data_ptr(), 1, 40, 40,
+                                self.out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        self.unsplit = self.out.clone()
+        assert not torch.equal(self.cut, self.unsplit)
+        assert_close(to_f64(self.cut), to_f64(self.unsplit), "cut against unsplit")
+
+    def call(self, stream=None):
+        hswa.prefill(self.layer, self.shape, self.kv.cache, self.q, self.k, self.v, self.cu, self.pre, 40, self.out,
+                     stream=stream)
+
+    def run(self, stream=None):
+        self.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        self.call(stream)
+        torch.cuda.synchronize()
+        return self.out
+
+
+def test_prefill_stream_arguments(gpu_lib):
+    """A torch stream gives the cut call; a raw handle, and any other object with a
+    cuda_stream, the unsplit one."""
+    turn, side = _ShortTurn(), torch.cuda.Stream()
+
+    class Foreign:
+        cuda_stream = side.cuda_stream
+
+    assert torch.equal(turn.run(side), turn.cut)
+    with torch.cuda.stream(side):
+        assert torch.equal(turn.run(), turn.cut)
+    assert torch.equal(turn.run(torch.cuda.ExternalStream(side.cuda_stream)), turn.cut)
+    assert torch.equal(turn.run(side.cuda_stream), turn.unsplit)
+    assert torch.equal(turn.run(Foreign()), turn.unsplit)
+
+
+def test_prefill_without_memory_runs_unsplit(gpu_lib):
+    turn = _ShortTurn()
+    torch.cuda.empty_cache()
+    try:
+        torch.cuda.set_per_process_memory_fraction(1e-6)  # nothing more to be had from torch's allocator
+        assert torch.equal(turn.run(), turn.unsplit)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(turn.run(), turn.cut)
+
+
+def test_prefill_in_a_foreign_capture_runs_unsplit(gpu_lib):
+    """A graph captured through the runtime itself owns no memory of torch's: the
+    call takes none, and replays of the graph give the unsplit bits while torch's
+    allocator hands the memory out again."""
+    turn, side = _ShortTurn(), torch.cuda.Stream()
+    hip = ctypes.CDLL("libamdhip64.so.7")  # the one that is loaded
+    handle, graph, exe = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_void_p()
+
+    def check(status):
+        assert status == 0, f"HIP error {status}"
+
+    torch.cuda.synchronize()
+    check(hip.hipStreamBeginCapture(handle, 2))  # relaxed: no other call of this thread is restricted
+    try:
+        turn.call(side)
+    finally:
+        check(hip.hipStreamEndCapture(handle, ctypes.byref(graph)))
+    check(hip.hipGraphInstantiate(ctypes.byref(exe), graph, None, None, ctypes.c_size_t(0)))
+    for _ in range(3):
+        turn.out.fill_(float("nan"))
+        taken = [torch.full((16 << 20,), float("nan"), device="cuda") for _ in range(3)]
+        torch.cuda.synchronize()
+        check(hip.hipGraphLaunch(exe, handle))
+        torch.cuda.synchronize()
+        assert torch.equal(turn.out, turn.unsplit)
+        assert all(torch.isnan(t).all() for t in taken)
+        del taken
+    check(hip.hipGraphExecDestroy(exe))
+    check(hip.hipGraphDestroy(graph))
