@@ -365,7 +365,7 @@ def _prefill_scratch(nbytes: int, stream):
         return None
     with torch.cuda.stream(stream):
         try:
-            t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+            t = torch.UntypedStorage(nbytes, device="cuda")  # (deterministic mode would fill a new tensor)
         except torch.cuda.OutOfMemoryError:
             return None
         if torch.cuda.is_current_stream_capturing() and not _in_private_pool(t):

@@ -181,6 +181,27 @@ def test_prefill_without_memory_runs_unsplit(gpu_lib):
     assert torch.equal(turn.run(), turn.cut)
 
 
+def test_prefill_scratch_is_not_filled(gpu_lib):
+    """Deterministic mode fills the memory of new tensors; the scratch is none."""
+    turn = _ShortTurn()
+    fills = []
+
+    class Watch(torch.utils._python_dispatch.TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            fills.append(str(func))
+            return func(*args, **(kwargs or {}))
+
+    torch.use_deterministic_algorithms(True)
+    try:
+        with Watch():
+            turn.call()
+    finally:
+        torch.use_deterministic_algorithms(False)
+    torch.cuda.synchronize()
+    assert fills == []
+    assert torch.equal(turn.out, turn.cut)
+
+
 def test_prefill_in_a_foreign_capture_runs_unsplit(gpu_lib):
     """A graph captured through the runtime itself owns no memory of torch's: the
     call takes none, and replays of the graph give the unsplit bits while torch's
