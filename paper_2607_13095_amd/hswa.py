@@ -375,9 +375,13 @@ def _prefill_scratch(nbytes: int, stream):
 
 def _in_private_pool(t) -> bool:
     """Whether the memory belongs to a graph's (or another private) pool."""
+    try:
+        segments = _torch().cuda.memory_snapshot()
+    except RuntimeError:  # an allocator without snapshots
+        return False
     a = t.data_ptr()
     return any(s["address"] <= a < s["address"] + s["total_size"] and tuple(s["segment_pool_id"]) != (0, 0)
-               for s in _torch().cuda.memory_snapshot())
+               for s in segments)
 
 
 def prefill(layer: Layer, shape: Shape, cache: Cache, q, k_new, v_new, cu_seqlens, prefix_lens,

@@ -202,6 +202,26 @@ def test_prefill_scratch_is_not_filled(gpu_lib):
     assert torch.equal(turn.out, turn.cut)
 
 
+def test_prefill_captured_over_an_allocator_without_snapshots(gpu_lib, monkeypatch):
+    """Where torch's allocator cannot tell whose memory it is, a captured call runs
+    unsplit, as if there were none."""
+    turn = _ShortTurn()
+
+    def none():
+        raise RuntimeError("this allocator does not support snapshots")
+
+    monkeypatch.setattr(torch.cuda, "memory_snapshot", none)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        turn.call()
+    for _ in range(3):
+        turn.out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(turn.out, turn.unsplit)
+
+
 def test_prefill_in_a_foreign_capture_runs_unsplit(gpu_lib):
     """A graph captured through the runtime itself owns no memory of torch's: the
     call takes none, and replays of the graph give the unsplit bits while torch's
