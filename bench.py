@@ -58,8 +58,8 @@ MEASURED_TRAFFIC = {
                             "sha256": "cdcc305f60ae71c94206e8c0d2564ac45a53f925a071106fd327cd0aad5e8f2b",
                             "fetch_bytes": 8609264647, "write_bytes": 5574745},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
-                     "sha256": "052d7f427303f17bf18e6bacd431e69d3fefee04e093a3b9a1d8c2fd8f175dc6",
-                     "fetch_bytes": 453172322, "write_bytes": 141393401},
+                     "sha256": "30b227653aa81e4c516db740ab1fb44b799a548790a265a7a870c6c6087c80d2",
+                     "fetch_bytes": 452861001, "write_bytes": 141416915},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
                     "sha256": "d173b36396310cb48859492145807887f499ddfbe6dda8bf7370ffd648c95153",
                     "fetch_bytes": 184856219, "write_bytes": 147176827},

@@ -722,15 +722,21 @@ __device__ __forceinline__ void prefill_tiles(const PrefillParams &p0, TileBufs 
     }
   };
 
-  // the first three tiles' loads go out together (no accumulator is live yet)
+  // the first three tiles' loads go out together (no accumulator is live yet),
+  // those that exist: one tile loaded three times took 34 tokens over none 9.4 us
+  // instead of 8.8
   Stage st;
   {
     Stage s0, s1;
     fetch(0, s0);
-    fetch(min(1, ntiles - 1), s1);
-    fetch(min(2, ntiles - 1), st);
-    store_tile(0, s0);
-    if (ntiles > 1) store_tile(1, s1);
+    if (ntiles > 1) {
+      fetch(1, s1);
+      if (ntiles > 2) fetch(2, st);
+      store_tile(0, s0);
+      store_tile(1, s1);
+    } else {
+      store_tile(0, s0);
+    }
   }
   __syncthreads();
   const bool lag = wave >= kThreads / kWave / 2;  // group B
