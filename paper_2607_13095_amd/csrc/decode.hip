@@ -53,10 +53,12 @@ constexpr int kCols = 16;  // query heads per item (MFMA columns)
 constexpr int kMergeThreads = 256;
 // Up to this many rows a merged row has a workgroup of its own: with one wave
 // each, 64 rows of 65 pieces took as long as 8192 rows of few (1 x 16K, 64 heads:
-// 25.9 us a step against 23.9; 1 x 32K, 16 heads: 27.1 against 22.9); from about
-// 1024 rows on the further waves only cost (32 x 0.5-16K, 32 heads: 191.5
-// against 193).
-constexpr int kWideMergeRows = 512;
+// 25.9 us a step against 23.9; 1 x 32K, 16 heads: 27.1 against 22.9; 256 rows,
+// 4 x 4000 and 4 x 8000, 64 heads: 21.6 and 32.8 against 21.2 and 32.5). More rows
+// fill the device with one wave each, and the further waves only cost (384 rows,
+// 6 x 2-4K: 24.3 against 25.1; 512 rows, 8 x 1000 and 8 x 8000: 16.0 and 53.4
+// against 16.6 and 53.7).
+constexpr int kWideMergeRows = 256;
 constexpr float kRescaleLog2 = 8.f;  // lazy raise threshold of the running maximum (exp2 units)
 
 // Per-wave copy of a window of the block table: lane i holds the physical page
@@ -659,9 +661,10 @@ void decode_kernel(DecodeParams p) {
 }
 
 // Log-sum-exp merge of the split partials: kRowWaves waves per (sequence,
-// query, head) row, each taking every kRowWaves-th block of 16 pieces. Lane j reads the log-sum-exp of pieces j, j+64, ...; the weights are then
-// broadcast by readlane while the two half-waves accumulate even and odd
-// pieces, four output dims a lane (16-byte loads, 16 pieces in flight a step).
+// query, head) row, each taking every kRowWaves-th block of 16 pieces. Lane j
+// reads the log-sum-exp of pieces j, j+64, ...; the weights are then broadcast by
+// readlane while the two half-waves accumulate even and odd pieces, four output
+// dims a lane (16-byte loads, 16 pieces in flight a step).
 template <int kRowWaves>
 __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(DecodeParams p) {
   constexpr int kMergeWaves = kMergeThreads / kWave;

@@ -12,11 +12,12 @@
 // add. The chunk a tile will need next is loaded into registers while the tile
 // computes (waves 0-7 carry its V, waves 8-15 its K); each wave loads its
 // next tile's queries when a tile begins, a whole tile ahead (after the last
-// QK^T of the tile instead: 3% slower at 4 x 2048 over 8192, 88.0 against 85.5
-// us on inputs that are not in the memory-side cache); waves run through a tile's chunks without barriers (one
-// barrier per tile). Tiles whose positions all exist issue their loads and
-// stores unconditionally, so the memory counters stay exact along the loop
-// and no wait covers more than the operation it is for.
+// QK^T of the tile instead, 4 x 2048 over 8192: 85.3 us against 78.9 on inputs that
+// are not in the memory-side cache, 67.1 against 70.4 on inputs that are; 1 x
+// 3260 over none 42.1 against 38.3, and 34.2 against 35.0); waves run through a
+// tile's chunks without barriers (one barrier per tile). Tiles whose positions
+// all exist issue their loads and stores unconditionally, so the memory counters
+// stay exact along the loop and no wait covers more than the operation it is for.
 //
 // Used when G >= 8 and W + 256 / G - 1 <= 160: a tile then spans at most 7
 // chunks and the next tile adds at most one, so the ring of 8 is never short.

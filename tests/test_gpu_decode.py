@@ -185,3 +185,11 @@ def test_decode_full_few_spans(gpu_lib, pg, ctx):
     assert hswa.decode_split_len(hswa.Shape(16, 8, 128, pg), 1, ctx + 1) == 256
     gpu, ref = run_decode("full", 0, pg, 16, 8, [ctx], (212, pg, ctx))
     assert_close(gpu, ref, f"few spans pg={pg} ctx={ctx}")
+
+
+@pytest.mark.parametrize("ns", [16, 17])
+def test_decode_full_merge_rows(gpu_lib, ns):
+    """256 rows are merged by a workgroup each, 272 by a wave each."""
+    print(f"[decode-full-merge-rows] ns={ns}", flush=True)
+    gpu, ref = run_decode("full", 0, 64, 16, 2, [300 * (b + 1) for b in range(ns)], (213, ns))
+    assert_close(gpu, ref, f"merge of {ns * 16} rows")
