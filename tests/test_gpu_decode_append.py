@@ -220,3 +220,54 @@ def test_decode_append_pg16_invalid_page(gpu_lib):
         table[3, 639 // 16] = -1
 
     check(run_step("full", 0, 16, 64, 8, lens, (309,), table_edit=edit), "pg16 invalid page", oracle=False)
+
+
+@pytest.mark.parametrize("kind,window", [("swa", 128), ("swa_paged", 100), ("full", 0)])
+@pytest.mark.parametrize("ns", [64, 65])
+def test_decode_append_pg16_items(gpu_lib, kind, window, ns):
+    """512 workgroups of 16-key pages take the fused kernel, more the append and
+    the decode; windows that begin in the second page of a chunk among them."""
+    print(f"[decode-append pg16 items] {kind} W={window} ns={ns}", flush=True)
+    lens = [0 if b == 7 else 1 + (37 * b) % 250 for b in range(ns)] if kind == "full" else [1 + 23 * b for b in range(ns)]
+    check(run_step(kind, window, 16, 8, 8, lens, (310, window, ns)), f"{kind} W={window} ns={ns}")
+
+
+def _step_us(window, ns):
+    """us per fused step and per append + decode of ns sequences (64 / 8 heads, PG 16)."""
+    shape, layer = hswa.Shape(64, 8, D, 16), hswa.Layer.swa(window)
+    ctx = [1000 + 17 * b for b in range(ns)]
+    kv = LayerKV(layer, shape, ctx, fill=0.0)
+    q = torch.randn((ns, 64, D), device="cuda").to(torch.bfloat16)
+    k = torch.randn((ns, 8, D), device="cuda").to(torch.bfloat16)
+    lens, cu, pos, out = i32(ctx), i32(range(ns + 1)), i32([c - 1 for c in ctx]), torch.empty_like(q)
+
+    def step():
+        hswa.decode_append(layer, shape, kv.cache, q, k, k, lens, max(ctx), out)
+
+    def two():
+        hswa.kv_append(layer, shape, kv.cache, k, k, cu, pos)
+        hswa.decode(layer, shape, kv.cache, q, lens, max(ctx), out)
+
+    best = []
+    for fn in (step, two):
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            fn()
+            a.record()
+            for _ in range(20):
+                fn()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 50)
+        best.append(min(times))
+    return best
+
+
+def test_decode_append_pg16_large_batches(gpu_lib):
+    """A step is no slower than the append and the decode one after the other, also
+    where the batch is larger than the fused kernel's range (512 sequences: 91
+    us fused, 71 in two launches)."""
+    step, two = _step_us(128, 512)
+    print(f"[decode-append pg16 large] step {step:.1f} us, append + decode {two:.1f} us", flush=True)
+    assert step < 1.1 * two
