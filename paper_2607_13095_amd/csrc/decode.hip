@@ -320,13 +320,19 @@ void decode_kernel(DecodeParams p) {
       }
 
       // Pages of a chunk: one (PG >= 32), or two of 16 keys, of which a lane
-      // reads the one that holds its K rows (r >> 3) and its V keys (q >> 1).
+      // reads the one that holds its K rows (r >> 3) and its V keys (q >> 1). Of a
+      // whole range's chunk a page that holds no key of the range, or is invalid,
+      // is not read: its lanes read the other one again (a window of 128 keys is
+      // 8 or 9 pages of the 10 its chunks cover; 512 sequences, 64 / 8 heads: 55.9
+      // us with them, 53.9 without).
+      constexpr bool kOther = !kOnePage && !kSplit;
       auto page_base = [&](int cbase, int page) {  // byte offset of the chunk's first block, or of the page
         const int64_t ph = ((int64_t)max(page, 0) * hkv + g) << (shift + kHeadDimShift + 1);
         return kOnePage ? ph + ((int64_t)((cbase & (pg - 1)) >> 5) << (5 + kHeadDimShift + 1)) : ph;
       };
       auto issue_k = [&](int c, ChunkPages pages, Chunk &ch) {
         const int cbase = cfirst + c * kChunk;
+        if constexpr (kOther) pages = ChunkPages{pages.a >= 0 ? pages.a : pages.b, pages.b >= 0 ? pages.b : pages.a};
         int64_t o = page_base(cbase, pages.a);
         if constexpr (!kOnePage) o = r & 8 ? page_base(cbase, pages.b) : o;
         const char *kbase = reinterpret_cast<const char *>(pv.k_pool) + o;
@@ -338,12 +344,11 @@ void decode_kernel(DecodeParams p) {
       };
       auto issue_v = [&](int c, ChunkPages pages, Chunk &ch) {
         const int cbase = cfirst + c * kChunk;
-        int64_t o = page_base(cbase, pages.a);
         int page = pages.a;
-        if constexpr (!kOnePage) {
-          o = q & 2 ? page_base(cbase, pages.b) : o;
-          page = q & 2 ? pages.b : page;
-        }
+        if constexpr (!kOnePage) page = q & 2 ? pages.b : page;
+        if constexpr (kOther) pages = ChunkPages{pages.a >= 0 ? pages.a : pages.b, pages.b >= 0 ? pages.b : pages.a};
+        int64_t o = page_base(cbase, pages.a);
+        if constexpr (!kOnePage) o = q & 2 ? page_base(cbase, pages.b) : o;
         const char *vbase = reinterpret_cast<const char *>(pv.v_pool) + o;
         ch.kv0 = cbase + 8 * q;
         ch.vok = page >= 0;
@@ -433,8 +438,11 @@ void decode_kernel(DecodeParams p) {
           const int lp = (cfirst + c * kChunk) >> shift;
           constexpr int kMore = kOnePage ? 0 : 1;  // further pages of the chunk
           if (lp + kMore - tab.lp0 >= kWave) load_lane_table(tab, pv, b, lp, last_lp, lane);
-          return ChunkPages{__builtin_amdgcn_readlane(tab.page, lp - tab.lp0),
-                            __builtin_amdgcn_readlane(tab.page, lp - tab.lp0 + kMore)};
+          ChunkPages pages{__builtin_amdgcn_readlane(tab.page, lp - tab.lp0),
+                           __builtin_amdgcn_readlane(tab.page, lp - tab.lp0 + kMore)};
+          if constexpr (kOther)
+            if (cfirst + c * kChunk + 16 <= kb) pages.a = -1;  // wholly before the range
+          return pages;
         };
         // this wave's chunks: c0, c0 + kCoop, ...
         const int nw = nchunks > c0 ? (nchunks - c0 + kCoop<kSplit> - 1) / kCoop<kSplit> : 0;
