@@ -222,6 +222,35 @@ def test_decode_append_pg16_invalid_page(gpu_lib):
     check(run_step("full", 0, 16, 64, 8, lens, (309,), table_edit=edit), "pg16 invalid page", oracle=False)
 
 
+@pytest.mark.parametrize("pg", [16, 32, 64])
+@pytest.mark.parametrize("hq", [16, 32, 64])
+def test_decode_append_split_chunks(gpu_lib, pg, hq):
+    """The split decode puts the token's key into the last chunk of a span, which is
+    the first or the second one of its loop, alone or after others, for one and
+    for two 16-column groups a wave: single sequences and a batch, with NaN in the
+    token's slot, against the append and the decode (the same bits)."""
+    print(f"[decode-append split] PG={pg} {hq}/1", flush=True)
+    shape, layer = hswa.Shape(hq, 1, D, pg), hswa.Layer.full()
+    lens = [257, 273, 288, 289, 300, 324, 337, 356, 391, 513, 529, 545, 600, 777, 1025, 1100]
+    for seqs in [[n] for n in lens] + [lens]:
+        cu, ns = synth.cu_seqlens(seqs), len(seqs)
+        g = torch.Generator(device="cuda").manual_seed(len(seqs) * 10000 + seqs[0])
+        q, k, v = (torch.randn((m, h, D), generator=g, device="cuda").to(torch.bfloat16)
+                   for m, h in ((ns, hq), (sum(seqs), 1), (sum(seqs), 1)))
+        last = torch.tensor([int(c) - 1 for c in cu[1:]], device="cuda")
+        kv, ctx, out = LayerKV(layer, shape, seqs), i32(seqs), [torch.empty_like(q) for _ in range(2)]
+        cached = torch.ones(sum(seqs), dtype=torch.bool, device="cuda")
+        cached[last] = False
+        hswa.kv_append(layer, shape, kv.cache, k[cached], v[cached], i32(synth.cu_seqlens([n - 1 for n in seqs])),
+                       i32([0] * ns))
+        ws = torch.empty(hswa.decode_workspace_bytes(shape, ns, max(seqs)), dtype=torch.uint8, device="cuda")
+        hswa.decode_append(layer, shape, kv.cache, q, k[last], v[last], ctx, max(seqs), out[0], workspace=ws)
+        hswa.decode(layer, shape, kv.cache, q, ctx, max(seqs), out[1], workspace=ws)
+        torch.cuda.synchronize()
+        assert not torch.isnan(out[1]).any()
+        assert torch.equal(out[0], out[1]), f"{seqs}"
+
+
 @pytest.mark.parametrize("kind,window", [("swa", 128), ("swa_paged", 100), ("full", 0)])
 @pytest.mark.parametrize("ns", [64, 65])
 def test_decode_append_pg16_items(gpu_lib, kind, window, ns):
