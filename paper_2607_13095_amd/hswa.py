@@ -1,10 +1,12 @@
-"""Python binding of libhswa (ctypes): argument marshalling only.
+"""Python binding of libhswa (ctypes).
 
 Every call checks device, dtype, contiguity and sizes of the torch tensors it
 is given, passes their device pointers and the current HIP stream to the C ABI
-(``include/hswa.h``) and raises ``HswaError`` on a non-OK status. All compute
-runs in the library's HIP kernels; there is no fallback of any kind: if
-``libhswa.so`` is not built, ``load()`` raises.
+(``include/hswa.h``) and raises ``HswaError`` on a non-OK status. The binding
+allocates no device memory, but for ``prefill``'s scratch, which it takes from
+torch's caching allocator for the length of the call. All compute runs in the
+library's HIP kernels; there is no fallback of any kind: if ``libhswa.so`` is
+not built, ``load()`` raises.
 """
 
 from __future__ import annotations

@@ -8,11 +8,11 @@ layer B runs hswa_kv_append of that token, then hswa_decode. The checks:
     the fused store is exactly the append;
   * A's output matches B's within the same tolerance.
 The cases span the kernels behind the call (the fused one for SWA windows
-and short FULL contexts at PG >= 32; the split decode storing the token for
-longer FULL contexts at PG >= 32; the append kernel plus the decode kernels
-for PG 16 and windows over 8 chunks), windows
-around chunk and page sizes, GQA groups 1 to 32, empty sequences and an
-invalid page under the new token."""
+and short FULL contexts, with PG 16 up to 512 workgroups; the split decode
+storing the token for longer FULL contexts; the append kernel plus the decode
+kernel for larger batches on PG 16 and windows over 8 chunks), windows around
+chunk and page sizes, GQA groups 1 to 64, empty sequences and an invalid page
+under the new token."""
 
 import numpy as np
 import pytest

@@ -1,5 +1,6 @@
 """HIP-graph capture of the decode and prefill calls (the library enqueues
-kernels only: no allocation, no memset): a captured step (kv_append + decode
+kernels only: no allocation, no memset; the binding's prefill takes its scratch
+from the graph's own pool): a captured step (kv_append + decode
 for an SWA and a FULL layer) and a captured chunked prefill are replayed
 several times, with eager work of the program and synchronizations between the
 replays, and every replay's outputs are compared bit for bit with the eager

@@ -214,7 +214,7 @@ def test_prefill_split(gpu_lib, pg, hq, hkv, prefixes, chunks):
 
 @pytest.mark.parametrize("prefix,chunk", [(130, 70), (0, 40), (1500, 40)])
 def test_prefill_split_table_larger_than_context(gpu_lib, prefix, chunk):
-    """The split is chosen by what the block table can hold; contexts far shorter
+    """Scratch is taken by what the block table can hold; contexts far shorter
     than that run as whole tiles (the first two) or in short spans."""
     print(f"[prefill-split] table for 9000, {chunk} over {prefix}", flush=True)
     shape = hswa.Shape(32, 4, 128, 64)
