@@ -277,8 +277,9 @@ hswa_status hswa_decode(hswa_layer layer, const hswa_shape *shape, const hswa_ca
  * from k_new / v_new (results equal the two calls' up to rounding order); so
  * do the split-KV decode kernels of longer FULL layers (the log-sum-exp merge
  * still follows). Windows that touch more than 8 chunks of 32 keys, and with
- * page_size 16 batches of more than 512 (sequence, KV head, 16 query heads)
- * items, run the append kernel, then the decode kernel.
+ * page_size 16 windows or contexts of more than 4 chunks in batches of more than
+ * 512 (sequence, KV head, 16 query heads) items, run the append kernel, then the
+ * decode kernel.
  * k_new, v_new: device bf16 [ns][Hkv][D]; the other arguments as hswa_decode.
  * The call must not overlap another call writing the same layer's pools. */
 hswa_status hswa_decode_append(hswa_layer layer, const hswa_shape *shape, const hswa_cache *cache,

@@ -259,18 +259,22 @@ static int range_chunks(const DecodeParams &p) {
   return p.pool.window > 0 ? min(ctx_chunks, (p.pool.window + kAChunk - 2) / kAChunk + 1) : ctx_chunks;
 }
 
-// With 16-key pages only up to 512 workgroups: beyond them the append and the decode
-// as two launches are faster, whose workgroups of four waves hold more items at
-// once than this kernel's of up to eight (64 / 8 heads, us a step fused / in two
-// launches: W = 128, 32 sequences 8.1 / 10.3, 64 14.8 / 14.9, 65 18.1 / 15.1, 128
-// 27.4 / 23.4, 512 90.4 / 71.2; 100 - 255 cached tokens of a FULL layer, 64 15.8 /
-// 16.4, 65 18.4 / 17.7, 512 100.6 / 87.6).
+// With 16-key pages workgroups of more than four waves only up to 512 of them:
+// beyond that the append and the decode as two launches are faster, whose
+// workgroups of four waves hold more items at once. With fewer waves this kernel's
+// hold as many and save the launch (64 / 8 heads, us a step fused / in two
+// launches: W = 128, 5 waves, 32 sequences 8.1 / 10.3, 64 14.8 / 14.9, 65 15.2 /
+// 11.9, 128 24.6 / 20.5, 512 90.6 / 72.5; W = 96, 4 waves, 65 8.7 / 10.4, 128
+// 15.9 / 17.3, 512 59.9 / 60.5; W = 16, 2 waves, 128 8.2 / 12.3, 512 30.1 / 35.2;
+// a FULL layer's 250 cached tokens, 512 126 / 114, its 120 65.7 / 67.0).
 constexpr int64_t kAMaxItems16 = 512;
+constexpr int kASmallWaves16 = 4;
 
 bool decode_append_fused(const DecodeParams &p) {
   const int64_t items = (int64_t)p.ns * p.hkv * ((p.group + kACols - 1) / kACols);
-  return p.nq == 1 && p.max_splits == 1 && range_chunks(p) <= kAMaxWaves &&
-         (p.pool.pg_shift >= 5 || items <= kAMaxItems16);
+  const int nw = range_chunks(p);
+  return p.nq == 1 && p.max_splits == 1 && nw <= kAMaxWaves &&
+         (p.pool.pg_shift >= 5 || nw <= kASmallWaves16 || items <= kAMaxItems16);
 }
 
 hipError_t launch_decode_append(const DecodeParams &p, hipStream_t stream) {

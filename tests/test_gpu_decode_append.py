@@ -7,11 +7,11 @@ layer B runs hswa_kv_append of that token, then hswa_decode. The checks:
   * A's pools equal B's bit for bit (NaN-filled unused slots included), so
     the fused store is exactly the append;
   * A's output matches B's within the same tolerance.
-The cases span the kernels behind the call (the fused one for SWA windows
-and short FULL contexts, with PG 16 up to 512 workgroups; the split decode
-storing the token for longer FULL contexts; the append kernel plus the decode
-kernel for larger batches on PG 16 and windows over 8 chunks), windows around
-chunk and page sizes, GQA groups 1 to 64, empty sequences and an invalid page
+The cases span the kernels behind the call (the fused one for SWA windows and
+short FULL contexts, with PG 16 up to 4 chunks or 512 workgroups; the split
+decode storing the token for longer FULL contexts; the append kernel plus the
+decode kernel for larger batches on PG 16 and windows over 8 chunks), windows
+around chunk and page sizes, GQA groups 1 to 64, empty sequences and an invalid page
 under the new token."""
 
 import numpy as np
@@ -251,11 +251,12 @@ def test_decode_append_split_chunks(gpu_lib, pg, hq):
         assert torch.equal(out[0], out[1]), f"{seqs}"
 
 
-@pytest.mark.parametrize("kind,window", [("swa", 128), ("swa_paged", 100), ("full", 0)])
+@pytest.mark.parametrize("kind,window", [("swa", 128), ("swa_paged", 100), ("full", 0), ("swa", 97), ("swa", 98)])
 @pytest.mark.parametrize("ns", [64, 65])
 def test_decode_append_pg16_items(gpu_lib, kind, window, ns):
-    """512 workgroups of 16-key pages take the fused kernel, more the append and
-    the decode; windows that begin in the second page of a chunk among them."""
+    """512 workgroups of 16-key pages take the fused kernel, more of over 4 waves
+    the append and the decode; windows that begin in the second page of a chunk
+    among them."""
     print(f"[decode-append pg16 items] {kind} W={window} ns={ns}", flush=True)
     lens = [0 if b == 7 else 1 + (37 * b) % 250 for b in range(ns)] if kind == "full" else [1 + 23 * b for b in range(ns)]
     check(run_step(kind, window, 16, 8, 8, lens, (310, window, ns)), f"{kind} W={window} ns={ns}")
@@ -300,3 +301,11 @@ def test_decode_append_pg16_large_batches(gpu_lib):
     step, two = _step_us(128, 512)
     print(f"[decode-append pg16 large] step {step:.1f} us, append + decode {two:.1f} us", flush=True)
     assert step < 1.1 * two
+
+
+def test_decode_append_pg16_large_batches_small_windows(gpu_lib):
+    """A window of at most 4 chunks stays in the fused kernel whatever the batch
+    (512 sequences, W = 1: 21 us, 33 in two launches)."""
+    step, two = _step_us(1, 512)
+    print(f"[decode-append pg16 small windows] step {step:.1f} us, append + decode {two:.1f} us", flush=True)
+    assert step < 0.85 * two
