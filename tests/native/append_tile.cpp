@@ -27,8 +27,16 @@ int main() {
   expect(8, false, 32, 512, 8);
   expect(16, false, 32, 513, 8);
   expect(8, false, 33, 527, 8);  // fewer than 16 a sequence
-  expect(16, false, 20, 799, 8);
-  expect(32, false, 20, 800, 8);
+  expect(16, false, 20, 559, 8);
+  expect(32, false, 20, 560, 8);  // 28
+  // few heads: the workgroups of 8-token tiles count, not the tokens
+  expect(8, false, 1, 2048, 1);
+  expect(32, false, 1, 2049, 1);
+  expect(8, false, 128, 2048, 2);
+  expect(16, false, 128, 2049, 2);
+  expect(8, false, 27, 540, 1);
+  expect(8, false, 3, 240, 16);  // more than 8 heads: the tokens
+  expect(32, false, 3, 257, 16);
   // the grid: 8-token tiles up to one workgroup fewer than 2^32 threads take
   const int32_t ns = 1 << 21;  // fewer than 16 tokens a sequence
   expect(8, false, ns, (1 << 24) - 8, 8);

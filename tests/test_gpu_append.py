@@ -105,8 +105,11 @@ RUN_CASES = [
 
 
 @pytest.mark.parametrize("case", range(len(RUN_CASES)))
-def test_append_runs_bit_exact(gpu_lib, case):
+@pytest.mark.parametrize("heads", [0, 8])
+def test_append_runs_bit_exact(gpu_lib, heads, case):
+    """With the case's own head count, and with 8 (few heads take 8-token tiles)."""
     kind, window, pg, hkv, seqs = RUN_CASES[case]
+    hkv = heads or hkv
     print(f"[append-runs] case={case} kind={kind} W={window} PG={pg} Hkv={hkv} ns={len(seqs)}", flush=True)
     shape = hswa.Shape(hkv, hkv, 128, pg)
     starts = [s for s, _ in seqs]
