@@ -62,6 +62,12 @@ __device__ __forceinline__ int uniform_page(const PoolView &pv, int b, int lp) {
   return page >= 0 && page < pv.num_pages ? page : -1;
 }
 
+// Lane l's v (l wave-uniform), as a scalar.
+__device__ __forceinline__ int64_t lane64(int64_t v, int l) {
+  return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), l) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane((int)v, l));
+}
+
 // 4 x 4 transpose of dwords across the lanes l, l ^ 16, l ^ 32, l ^ 48: the
 // lane in 16-lane row m enters with dword j of its row m in t[j] and leaves
 // with dword m of rows 0..3 in w[0..3].
@@ -193,7 +199,7 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
     // aligned tokens among 256 single ones took 17.8 us instead of 10.6, and
     // 256 x 8 aligned tokens 15.3 instead of 7.7.)
     const int d = tid - kHeadDim;
-    const int64_t s0 = __shfl(sslot, 0, kWave);
+    const int64_t s0 = lane64(sslot, 0);
     const uint64_t in_row = __builtin_amdgcn_ballot_w64(lane < 8 && sslot == s0 + lane);
     if (in_row == 0xFFu && s0 >= 0 && (s0 & 7) == 0) {
       u32x4 w;
@@ -204,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int64_t s = __shfl(sslot, i, kWave);
+      const int64_t s = lane64(sslot, i);
       if (s >= 0) pv.v_pool[v_offset(pv, s >> pv.pg_shift, hkv, g, (int)(s & (pg - 1)), d)] = ev[i];
     }
     return;
@@ -247,8 +253,7 @@ __global__ __launch_bounds__(kThreads) void kv_append_kernel(AppendParams p) {
     runs &= runs - 1;
     const int rb = __builtin_amdgcn_readlane(b, l);
     const int rte = __builtin_amdgcn_readlane(te, l);
-    const int64_t rj = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(j >> 32), l) << 32) |
-                                 (uint32_t)__builtin_amdgcn_readlane((int)j, l));
+    const int64_t rj = lane64(j, l);
     const int64_t base = rj & ~(int64_t)(kRun - 1);
     const int first = (int)(rj - base);              // key of token t0 + l in the run
     const int nkeys = min(kRun, first + min(rte, p.total_tokens) - (t0 + l));  // key of the first token past the new ones
