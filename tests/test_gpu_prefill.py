@@ -326,3 +326,37 @@ def test_prefill_window_pages(gpu_lib, pg, prefix):
                      i32([0, chunk]), i32([prefix]), chunk, out)
         torch.cuda.synchronize()
         assert_close(to_f64(out), OA.prefill(OA.bf16_bits_to_f64(qb), kf, vf, prefix, window), f"PG {pg} bad {bad}")
+
+
+def _swa_prefill_us(prefix):
+    """us per SWA prefill of 4 x 16 tokens (64 / 8 heads, W = 128), from replays of a graph."""
+    shape, layer = hswa.Shape(64, 8, 128, 64), hswa.Layer.swa(128)
+    kv = LayerKV(layer, shape, [prefix + 16] * 4, fill=0.0)
+    q = torch.randn((64, 64, 128), device="cuda").to(torch.bfloat16)
+    k = torch.randn((64, 8, 128), device="cuda").to(torch.bfloat16)
+    cu, pre, out = i32(range(0, 65, 16)), i32([prefix] * 4), torch.empty_like(q)
+    call = lambda: hswa.prefill(layer, shape, kv.cache, q, k, k, cu, pre, 16, out)  # noqa: E731
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            call()
+    times = []
+    for _ in range(7):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        graph.replay()
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 50)
+    return min(times)
+
+
+def test_prefill_short_range_loads_its_own_chunks(gpu_lib):
+    """A short chunk over no prefix does not pay for the chunks of a whole window
+    (7.5 us; 8.9 with every chunk of the ring loaded. Over a full window 11.8)."""
+    short, full = _swa_prefill_us(0), _swa_prefill_us(2000)
+    print(f"[prefill-short] no prefix {short:.2f} us, over 2000 {full:.2f} us", flush=True)
+    assert short < 0.72 * full
