@@ -56,13 +56,13 @@ FLUSH_BYTES = 1 << 30  # a write this large evicts the 256 MB memory-side cache
 MEASURED_TRAFFIC = {
     "decode_full_stack70": {"sources": ["decode.hip", "hswa_common.h", "hswa_launch.h"],
                             "sha256": "ce8c8b087b183830db424f7da04debcfe929bc98eb2f6a243d11aaf7fb678adb",
-                            "fetch_bytes": 8609252517, "write_bytes": 5575554},
+                            "fetch_bytes": 8609245287, "write_bytes": 5575537},
     "prefill_full": {"sources": ["prefill.hip", "hswa_common.h", "hswa_launch.h"],
                      "sha256": "30b227653aa81e4c516db740ab1fb44b799a548790a265a7a870c6c6087c80d2",
-                     "fetch_bytes": 453091017, "write_bytes": 141411337},
+                     "fetch_bytes": 453089455, "write_bytes": 141397204},
     "prefill_swa": {"sources": ["prefill_run.hip", "hswa_common.h", "hswa_launch.h"],
-                    "sha256": "62397f29f59af853845bf8a6041076b645c540e57877bb2266585de25179ac1d",
-                    "fetch_bytes": 184879255, "write_bytes": 148286054},
+                    "sha256": "0dde1257a07c56f6bcecc1f026cbb7636c660e1de65fe935fbc2a3f1cbd3f217",
+                    "fetch_bytes": 184862370, "write_bytes": 147919465},
 }
 
 

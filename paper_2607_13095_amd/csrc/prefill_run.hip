@@ -320,24 +320,18 @@ __global__ __launch_bounds__(kRThreads) __attribute__((amdgpu_waves_per_eu(4))) 
 
   // ---- warm-up: the queries and the chunks of the first tile (at most 7), all
   // in flight at once (the accumulators are not live yet; two chunks at a time
-  // took 16.0 us for 300 tokens over 2000, against 14.7). A range of up to three
-  // chunks loads those only (4 x 16 tokens over none 7.5 us, 8.9 with seven
-  // loads); a longer one all seven, repeating its last, without branches between
-  // them (4 x 64 over 2000 13.3, 13.5 with them) ----
+  // took 16.0 us for 300 tokens over 2000, against 14.7). A short range loads its
+  // own chunks only: 4 x 16 tokens over none 7.6 us, 8.9 with seven loads whatever
+  // the range ----
   auto tile_last_key = [&](int t) { return P + min(C, (t + 1) * npos) - 1; };
   const int ce0 = chunk_of(tile_last_key(t0));
   int stored = ce0 + 1;  // next chunk to store
   RStage sa;
   {
     RStage sw[kRBufs - 1];
-    if (ce0 < 3) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (c <= ce0) fetch(c, sw[c]);
-    } else {  // past the last chunk repeats of it
-#pragma unroll
-      for (int c = 0; c < kRBufs - 1; ++c) fetch(min(c, ce0), sw[c]);
-    }
+    for (int c = 0; c < kRBufs - 1; ++c)
+      if (c <= ce0) fetch(c, sw[c]);
     load_q(t0, qf);
     fetch(stored, sa);  // the chunk the next tile adds
 #pragma unroll
